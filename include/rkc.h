@@ -60,7 +60,11 @@ extern "C" {
 #define RKC_METHOD_RKCK  1      /* Sec. 2.3, Table 1 */
 
 /* ---- launch schedule (never changes results: see rkc_integrate) --------- */
-#define RKC_SCHED_AUTO        0
+#define RKC_SCHED_AUTO        0  /* with few cells for the chip, one cell per wavefront (or
+                                    per workgroup, for large mechanisms), the lane groups'
+                                    arithmetic in the same order on more lanes; else as
+                                    RKC_SCHED_PERSISTENT, or _PLAIN when every cell is
+                                    resident */
 #define RKC_SCHED_PLAIN       1  /* one lane group per cell, grid covers all cells */
 #define RKC_SCHED_PERSISTENT  2  /* resident grid; groups pull cells from a device queue
                                     in index order (cells ordered by decreasing expected

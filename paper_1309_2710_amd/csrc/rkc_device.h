@@ -95,7 +95,7 @@ struct Tables {
 constexpr uint32_t TERM_MAX_BYTES = 0xffffu;
 
 struct Params {
-    int nS, N, NK, nU, RU, NSEG, SEGL, L2P, L2N;
+    int nS, N, NK, nU, nU_pad, RU, NSEG, SEGL, L2P, L2N;
     int RUp, NPR, NMS;               // first round with pressure-dependent units, their
                                      // rounds (RUp + NPR = RU), efficiency sets
     int RU2;                         // rounds [0, RU2): no side has a third reactant slot
@@ -400,15 +400,16 @@ constexpr double LOG2E = 1.44269504088896340736;     // log2(e)
 // tiny (|d| < 1e-6), log2 m = l0 + ln(1 + d) log2(e), and the series
 // d - d^2/2 + d^3/3 of ln(1 + d) leaves a truncation below d^4/4.  The error
 // is that of the exponential (about 1e-16 absolute) plus the final rounding.
-// No division and no polynomial table beyond the exponential's.
+// No division and no polynomial table beyond the exponential's.  A negative,
+// zero, infinite or NaN x needs no test: its l0 is NaN or infinite, and the
+// exponential's reduction y - n of an infinity is NaN.
 __device__ __forceinline__ double log2_pos(double x, const ExpK &k) {
     int e;
     const double m = frexp(x, &e);
     const double l0 = (double)__builtin_amdgcn_logf((float)m);
     const double d = __builtin_fma(m, exp2_b31(-l0, k), -1.0);
     const double l1 = d * __builtin_fma(d, __builtin_fma(d, 1.0 / 3.0, -0.5), 1.0);
-    const double r = (double)e + __builtin_fma(l1, LOG2E, l0);
-    return (x > 0.0 && x <= 0x1.fffffffffffffp+1023) ? r : __builtin_nan("");
+    return (double)e + __builtin_fma(l1, LOG2E, l0);
 }
 
 __device__ __forceinline__ double log2_pos(double x) { return log2_pos(x, exp_k()); }
@@ -422,7 +423,7 @@ __device__ __forceinline__ double log2_pos(double x) { return log2_pos(x, exp_k(
 __device__ __forceinline__ double rsixth_pos(double x) {
     int e;
     const double m = frexp(x, &e);
-    const int q = (e >= 0) ? e / 6 : -((5 - e) / 6);
+    const int q = (((e + 6000) * 43691) >> 18) - 1000;   // floor(e / 6), |e| <= 1100
     const double a = __builtin_ldexp(m, e - 6 * q);
     double y = (double)__builtin_amdgcn_exp2f(__builtin_amdgcn_logf((float)a) * (-1.0f / 6.0f));
 #pragma unroll

@@ -12,6 +12,7 @@
 #include "rkc.h"
 #include "rkc_internal.h"
 #include "rkc_lane.h"
+#include "rkc_wave.h"
 
 using rkcdev::NFIELD;
 using rkcdev::UNIT_DOUBLES;
@@ -124,7 +125,8 @@ constexpr int COEF_SMAX = 128;
 // (Sec. 2.4: Chebyshev values at w0 = 1 + kappa/s^2 by their recurrences,
 // b_j = T''_j / T'_j^2 for j >= 2, b_1 = 1/w0, b_0 = b_2, a_j = 1 - b_j T_j).
 std::vector<double> coef_table() {
-    std::vector<double> t(4 * (size_t)rkcdev::coef_offset(COEF_SMAX + 1), 0.0);
+    // one entry more than the last: the kernels load one stage ahead
+    std::vector<double> t(4 * (size_t)(rkcdev::coef_offset(COEF_SMAX + 1) + 1), 0.0);
     for (int s = 2; s <= COEF_SMAX; ++s) {
         const double w0 = 1.0 + rkcdev::KAPPA / ((double)s * (double)s);
         std::vector<double> T(s + 1), Tp(s + 1), Tpp(s + 1), b(s + 1);
@@ -323,6 +325,9 @@ int plan_gather(const rkc_mech *m, int G, int NK, int RU, GatherPlan *gp) {
     return RKC_OK;
 }
 
+// Rounds of the interleaved unit table in global memory.
+int il_rounds(int RU) { return (RU + 3) / 4 * 4 + 1; }
+
 int ensure_tables(rkc_mech *m, int G, int NK, int RU, NkTables **out, bool may_build = true) {
     for (auto &t : m->nk)
         if (t.NK == NK && t.G == G) { *out = &t; return RKC_OK; }
@@ -394,9 +399,10 @@ int ensure_tables(rkc_mech *m, int G, int NK, int RU, NkTables **out, bool may_b
     HIP_OK(hipMemcpy(t.gather2, gp.words2.data(), gp.words2.size() * 4, hipMemcpyHostToDevice));
     {
         // unit records lane-interleaved in 16-byte pieces (piece q of unit
-        // rG + g at double2 (4r + q)G + g), plus one zero round that the
-        // kernels' one-round-ahead read of the reactant slots may touch
-        std::vector<double> il((size_t)(RU + 1) * G * UNIT_DOUBLES, 0.0);
+        // rG + g at double2 (4r + q)G + g), plus zero rounds: one that the
+        // kernels' one-round-ahead read of the reactant slots may touch, and
+        // those that fill the last round of the kernels with several waves per cell
+        std::vector<double> il((size_t)il_rounds(RU) * G * UNIT_DOUBLES, 0.0);
         for (int u = 0; u < RU * G && u < m->nU_pad; ++u) {
             const int r = u / G, g = u % G;
             for (int q = 0; q < UNIT_DOUBLES / 2; ++q) {
@@ -703,6 +709,66 @@ int plan_launch(const rkc_mech *m, const Choice &ch, const void *kernel, size_t 
     return RKC_OK;
 }
 
+// The one-cell-per-wave form for this call, or null for the lane-group kernels.
+// Both give the same bits, so the choice may depend on the cell count; it is made
+// unless the plain schedule or a grain is asked for, which only the lane-group
+// kernels have.  Where the line lies (MI355X, RKC, dt 1e-6, ms,
+// lane groups against waves):
+//   9 species, 16 lanes    1,024 cells 9.2 / 2.6    4,096 9.4 / 4.0   16,384 10.3 / 12.5
+//   13 species, 16 lanes   4,099 3.7 / 1.4         65,536 15.5 / 8.5  262,144 21.2 / 29.6
+//   53 species, 64 lanes   1,031 6.9 / 2.8         32,768 38.8 / 33.3 131,072 142 / 127
+//   53 species, falloff    1,031 13.7 / 6.1        16,411 29.6 / 34.3
+//   111 species            512 45 / 16              2,048 40 / 23     8,192 73.9 / 70
+const rkchost::WaveDesc *pick_wave(const rkc_mech *m, const Choice &ch, const NkTables *nk,
+                                   size_t n, double atol, const rkc_opts &o) {
+    if (!nk || o.schedule == RKC_SCHED_PLAIN || o.block_groups != 0 || o.grid_blocks != 0)
+        return nullptr;
+    if (o.method == RKC_METHOD_RKC && atol < rkcdev::ATOL_WAVE) return nullptr;
+    int cnt = 0;
+    const rkchost::WaveDesc *t = rkchost::wave_variants(&cnt);
+    for (int i = 0; i < cnt; ++i) {
+        const rkchost::WaveDesc &d = t[i];
+        const int lanes = 64 * d.NW;
+        if (d.SG != ch.v.G || d.NSL != ch.v.NSL || d.pd != (m->n_pdep > 0)) continue;
+        // a requested placement is kept: only global records can be asked for here
+        if (o.param_placement != RKC_PARAMS_AUTO &&
+            !(o.param_placement == RKC_PARAMS_GLOBAL && d.UL == rkcdev::UNITS_GLOBAL))
+            continue;
+        if ((m->nU + lanes - 1) / lanes > d.RUC) continue;
+        // global records: whole rounds of the 64-lane table
+        if (d.UL == rkcdev::UNITS_GLOBAL && d.RUC * d.NW > il_rounds(ch.RU)) continue;
+        if (rkcdev::wave_segments(nk->NSEG, d.SG, lanes) > d.MS || nk->SEGL > d.SL) continue;
+        if (nk->L2P > d.LP || nk->L2N > d.LN) continue;
+        const double resident = (double)(4 * d.occ / d.NW) * m->num_cus;
+        if (d.fill > 0.0 && (double)n > d.fill * resident) continue;
+        return &d;
+    }
+    return nullptr;
+}
+
+// Workgroups of one cell (several waves per cell) or of up to one wave per SIMD
+// and target wave, fewer while that leaves compute units without one.
+int plan_wave_launch(const rkc_mech *m, const rkchost::WaveDesc &d, const NkTables *nk,
+                     const void *kernel, size_t n, const rkc_opts &o, Launch *L) {
+    const int lanes = 64 * d.NW;
+    const rkcdev::WaveShape sh{nk->NK, lanes, d.RUC, d.MS, nk->NPR, nk->NMS, d.SG, d.UL};
+    int cells = d.NW > 1 ? 1 : 4 * d.occ;
+    while (cells > 1 && (size_t)cells * (size_t)m->num_cus > n) cells = (cells + 1) / 2;
+    while (cells > 1 && rkcdev::wave_lds_bytes(sh, cells) > m->max_lds) --cells;
+    L->lds = rkcdev::wave_lds_bytes(sh, cells);
+    if (L->lds > m->max_lds) return RKC_ENOTSUP;
+    L->groups_per_block = cells;
+    L->threads = cells * lanes;
+    HIP_OK(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L->lds));
+    int per_cu = 0;
+    HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, L->threads, L->lds));
+    const size_t all = (n + cells - 1) / cells;
+    const size_t resident = (size_t)std::max(1, per_cu) * (size_t)m->num_cus;
+    L->persistent = o.schedule == RKC_SCHED_PERSISTENT || resident < all;
+    L->blocks = (int)std::min(all, resident);
+    return RKC_OK;
+}
+
 void fill_params(const rkc_mech *m, const Choice &ch, const NkTables *nk, rkcdev::Params *p) {
     std::memset(p, 0, sizeof(*p));
     p->nS = m->nS;
@@ -732,6 +798,7 @@ void fill_params(const rkc_mech *m, const Choice &ch, const NkTables *nk, rkcdev
     }
     p->NK = nk->NK;
     p->nU = m->nU;
+    p->nU_pad = m->nU_pad;
     p->RU = ch.RU;
     p->NSEG = nk->NSEG;
     p->SEGL = nk->SEGL;
@@ -749,6 +816,7 @@ void fill_params(const rkc_mech *m, const Choice &ch, const NkTables *nk, rkcdev
     p->invTmax = m->invTmax;
     p->NPR = nk->NPR;
     p->NMS = nk->NMS;
+    p->n_plain = m->n_plain;
     p->agg = m->agg_d;
     p->queue = m->queue_d;
     p->coef = m->coef_d;
@@ -805,7 +873,13 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
                                                     : (pd ? ch.v.k_rkck_pd : ch.v.k_rkck);
     if (!kernel) return RKC_ENOTSUP;
     Launch L;
-    rc = plan_launch(m, ch, kernel, n, o, true, nk, &L);
+    const rkchost::WaveDesc *wd = pick_wave(m, ch, nk, n, atol, o);
+    if (wd) {
+        kernel = o.method == RKC_METHOD_RKC ? wd->k_rkc : wd->k_rkck;
+        rc = plan_wave_launch(m, *wd, nk, kernel, n, o, &L);
+    } else {
+        rc = plan_launch(m, ch, kernel, n, o, true, nk, &L);
+    }
     if (rc) return rc;
     // launch errors are taken from the launch call itself: the thread's last
     // error can hold an unrelated earlier status (e.g. a not-ready query made
@@ -840,7 +914,8 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
     void *args[] = {&p};
     HIP_OK(hipLaunchKernel(kernel, dim3(L.blocks), dim3(L.threads), args, L.lds, st));
     li->G = ch.v.G;
-    li->RUC = ch.v.RUC;
+    li->RUC = !wd ? ch.v.RUC
+                  : wd->UL == rkcdev::UNITS_REG ? 1 : (wd->UL == rkcdev::UNITS_LDS ? 0 : -1);
     li->persistent = L.persistent;
     li->blocks = L.blocks;
     li->threads = L.threads;
@@ -861,6 +936,11 @@ int prepare(rkc_mech *m, const rkc_opts &o, size_t n_cells) {
         rc = plan_launch(m, ch, k, n_cells, o, true, nk, &L);
         if (rc) return rc;
     }
+    if (const rkchost::WaveDesc *wd = pick_wave(m, ch, nk, n_cells, 1.0, o))
+        for (const void *k : {wd->k_rkc, wd->k_rkck}) {
+            rc = plan_wave_launch(m, *wd, nk, k, n_cells, o, &L);
+            if (rc) return rc;
+        }
     return RKC_OK;
 }
 
@@ -1502,7 +1582,7 @@ int rkc_autotune(const rkc_mech *mc, size_t n, const double *T, const double *P,
     if (o.lanes_per_cell != 0) lanes_c = {o.lanes_per_cell};
     else lanes_c = {64, 32, 16, 8, 1};
     if (o.param_placement != RKC_PARAMS_AUTO) place_c = {o.param_placement};
-    else place_c = {RKC_PARAMS_LDS, RKC_PARAMS_GLOBAL, RKC_PARAMS_REGISTERS};
+    else place_c = {RKC_PARAMS_AUTO, RKC_PARAMS_LDS, RKC_PARAMS_GLOBAL, RKC_PARAMS_REGISTERS};
     struct Cand {
         rkc_opts c;
         float ms;
@@ -1514,6 +1594,18 @@ int rkc_autotune(const rkc_mech *mc, size_t n, const double *T, const double *P,
             Choice ch;
             if (choose_variant(m, G, pl, &ch) != RKC_OK) continue;
             if (pl == RKC_PARAMS_REGISTERS && ch.v.RUC <= 0) continue;   // fell back to LDS
+            if (pl == RKC_PARAMS_AUTO && o.param_placement == RKC_PARAMS_AUTO) {
+                // the automatic placement differs from the others only where
+                // it runs one cell per wave
+                rkc_opts a = o;
+                a.lanes_per_cell = G;
+                a.schedule = RKC_SCHED_PERSISTENT;
+                a.block_groups = a.grid_blocks = 0;
+                NkTables *nk = nullptr;
+                if (G == 1 || select_variant(m, a, &ch, &nk) != RKC_OK ||
+                    !pick_wave(m, ch, nk, n, atol, a))
+                    continue;
+            }
             if (pl == RKC_PARAMS_GLOBAL && (G == 1 || !find_variant(ch.v.G, ch.v.NSL, -1)))
                 continue;
             if (G == 1 && pl != RKC_PARAMS_LDS) continue;   // one placement for one lane per cell

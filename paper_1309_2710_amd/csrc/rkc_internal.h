@@ -30,6 +30,20 @@ const VariantDesc *variants_g8(int *n);
 // one lane per cell (G = 1, NSL = the state capacity NMAX of the kernel)
 const VariantDesc *variants_lane(int *n);
 
+// One compiled one-cell-per-wave form (rkc_wave.h) of the variant with SG lanes
+// per cell and NSL state elements per lane: NW waves per cell, at most RUC unit
+// rounds of 64 NW lanes with their parameters placed as UL says, MS gather
+// segments of at most SL terms, LP positive and LN negative pieces per state
+// slot, occ waves per SIMD; for plain or pressure-dependent mechanisms; used for
+// up to `fill` cells per resident one (0: any number).
+struct WaveDesc {
+    int SG, NSL, RUC, UL, NW, MS, SL, LP, LN, occ;
+    bool pd;
+    double fill;
+    const void *k_rkc, *k_rkck;
+};
+const WaveDesc *wave_variants(int *n);
+
 // Aggregate counters per launch (n_rhs, n_steps, n_reject, n_sigma,
 // n_power_iter, s_max_used, n_failed, worst_status, issued slots; rest spare).
 constexpr int AGG_N = 16;
