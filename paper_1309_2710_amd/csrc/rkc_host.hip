@@ -617,6 +617,7 @@ __global__ void reset_scratch_kernel(unsigned long long *agg, int *queue) {
     if (threadIdx.x == 0) *queue = 0;
 }
 
+
 struct Launch {
     int threads, blocks, groups_per_block;
     size_t lds;
@@ -766,6 +767,34 @@ int plan_wave_launch(const rkc_mech *m, const rkchost::WaveDesc &d, const NkTabl
     const size_t resident = (size_t)std::max(1, per_cu) * (size_t)m->num_cus;
     L->persistent = o.schedule == RKC_SCHED_PERSISTENT || resident < all;
     L->blocks = (int)std::min(all, resident);
+    return RKC_OK;
+}
+
+// Source-term launch of the lane-group variants: a grid that covers the chip
+// once (the kernel walks over the cells), in smaller workgroups while there are
+// too few cells to reach every compute unit, but with 512 lanes to stage the
+// tables.
+int plan_rhs_launch(const rkc_mech *m, const Choice &ch, const NkTables *nk, const void *kernel,
+                    size_t n, const rkc_opts &o, Launch *L) {
+    const int G = ch.v.G;
+    const rkcdev::Shape sh = shape_for(ch, nk);
+    int gpb = std::max(1, ch.v.max_threads / G);
+    if (o.block_groups > 0) {
+        gpb = std::min(gpb, o.block_groups);
+    } else {
+        while (gpb * G > 512 && (size_t)gpb * (size_t)m->num_cus > n) gpb = (gpb + 1) / 2;
+    }
+    while (gpb > 1 && rkcdev::lds_bytes(sh, gpb) > m->max_lds) --gpb;
+    L->groups_per_block = gpb;
+    L->threads = gpb * G;
+    L->lds = rkcdev::lds_bytes(sh, gpb);
+    if (L->lds > m->max_lds) return RKC_ENOTSUP;
+    HIP_OK(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L->lds));
+    int per_cu = 0;
+    HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, L->threads, L->lds));
+    const size_t all = (n + gpb - 1) / gpb;
+    L->blocks = (int)std::min(all, (size_t)std::max(1, per_cu) * (size_t)m->num_cus);
+    L->persistent = false;
     return RKC_OK;
 }
 
@@ -1304,7 +1333,8 @@ int rkc_rhs(const rkc_mech *mc, size_t n, const double *T, const double *P, cons
     Launch L;
     const void *krhs = m->n_pdep > 0 ? ch.v.k_rhs_pd : ch.v.k_rhs;
     if (!krhs) return RKC_ENOTSUP;
-    rc = plan_launch(m, ch, krhs, n, lo, false, nk, &L);
+    rc = ch.v.G == 1 ? plan_launch(m, ch, krhs, n, lo, false, nk, &L)
+                     : plan_rhs_launch(m, ch, nk, krhs, n, lo, &L);
     if (rc) return rc;
     rkcdev::Params p;
     fill_params(m, ch, nk, &p);
