@@ -28,7 +28,7 @@
  *   - units: T in K, P in Pa, Y mass fractions, dt in s; mechanism units are
  *     listed at rkc_mech_desc.
  *   - calls that share one rkc_mech handle must not overlap in time (they share
- *     the handle's device scratch: work-queue counter and statistics).
+ *     the handle's device scratch: work queue and statistics).
  */
 #ifndef RKC_H
 #define RKC_H
@@ -269,8 +269,8 @@ int rkc_integrate(const rkc_mech *mech, size_t n_cells, double *T, const double 
  * capture, tight serving loops, harnesses that forbid allocation):
  * rkc_integrate with device arrays (opts->device_ptrs must be 1, opts must not
  * be NULL) that calls no hipMalloc, hipFree or other allocating routine.  The
- * launch's scratch -- the aggregate counters and the work-queue head of the
- * kernels, 256 bytes -- is a file-scope device array of the library, one per
+ * launch's scratch -- the aggregate counters and the work-queue heads of the
+ * kernels, 2176 bytes -- is a file-scope device array of the library, one per
  * GPU, cleared by a kernel at the start of every call; the call's size limit is
  * that of rkc_integrate (RKC_MAX_CELLS cells, RKC_ENOTSUP above).  Results are
  * those of rkc_integrate with the same options.  The mechanism's tables for the

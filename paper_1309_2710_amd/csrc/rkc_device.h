@@ -116,7 +116,7 @@ struct Params {
                                      // coef_offset), or null
     int coef_smax;
     double invN;                     // 1 / N
-    int *queue;                      // persistent work-queue head
+    int *queue;                      // heads of the work queue's parts (see QUEUE_PARTS)
     int persistent;
     int groups_total;                // groups in the launched grid
     // element (cell, i) of Y is Y[cell * ycs + i * yss] and element (cell, k)
@@ -132,6 +132,13 @@ struct Params {
     int n_plain;                     // units [0, n_plain) have no pressure dependence
     int lane_rows;                   // LDS rows of 64 doubles per wave
 };
+
+// The work queue is dealt out in QUEUE_PARTS parts: claim i of part q is position
+// groups_total + i QUEUE_PARTS + q.  Claims on one address are served one by
+// one, 11.4 ns each from anywhere on the chip (a single head held 262,144 cells
+// of 10 evaluations to 1.75 ms, now 1.06); 16 heads on lines of their own take
+// 0.7 ns, and 64 measured the same.
+constexpr int QUEUE_PARTS = 16, QUEUE_STRIDE = 32, QUEUE_INTS = QUEUE_PARTS * QUEUE_STRIDE;
 
 // RKC stage coefficients (E:rkc1, E:rkcj) depend on the stage count s and
 // the stage j only.  For s <= coef_smax they are read from a table of 4

@@ -614,7 +614,7 @@ int ensure_stage(rkc_mech *m, size_t bytes) {
 
 __global__ void reset_scratch_kernel(unsigned long long *agg, int *queue) {
     if (threadIdx.x < AGG_N) agg[threadIdx.x] = 0ull;
-    if (threadIdx.x == 0) *queue = 0;
+    for (int i = threadIdx.x; i < rkcdev::QUEUE_INTS; i += blockDim.x) queue[i] = 0;
 }
 
 
@@ -916,7 +916,7 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
     {
         void *rargs[] = {&agg_d, &queue_d};
         HIP_OK(hipLaunchKernel(reinterpret_cast<const void *>(&reset_scratch_kernel), dim3(1),
-                               dim3(64), rargs, 0, st));
+                               dim3(512), rargs, 0, st));
     }
     rkcdev::Params p;
     fill_params(m, ch, nk, &p);
@@ -1258,7 +1258,7 @@ int rkc_mech_create(const rkc_mech_desc *d, rkc_mech **out) {
         m->max_lds = prop.sharedMemPerBlock;
         if (hipMalloc(&m->units_d, m->units_h.size() * 8) != hipSuccess ||
             hipMalloc(&m->agg_d, AGG_N * sizeof(unsigned long long)) != hipSuccess ||
-            hipMalloc(&m->queue_d, sizeof(int)) != hipSuccess)
+            hipMalloc(&m->queue_d, rkcdev::QUEUE_INTS * sizeof(int)) != hipSuccess)
             rc = RKC_ENOMEM;
         else if (hipMemcpy(m->units_d, m->units_h.data(), m->units_h.size() * 8,
                            hipMemcpyHostToDevice) != hipSuccess)
@@ -1497,7 +1497,7 @@ int rkc_graph_create(const rkc_mech *mc, size_t n, double *T, const double *P, d
     hipStream_t cap = nullptr;
     rkchost::LaunchInfo li;
     if (hipMalloc(&g->agg_d, AGG_N * sizeof(unsigned long long)) != hipSuccess ||
-        hipMalloc(&g->queue_d, sizeof(int)) != hipSuccess)
+        hipMalloc(&g->queue_d, rkcdev::QUEUE_INTS * sizeof(int)) != hipSuccess)
         rc = RKC_ENOMEM;
     if (rc == RKC_OK) rc = rkchost::prepare(m, o, n);
     if (rc == RKC_OK &&

@@ -80,15 +80,47 @@ __device__ __forceinline__ void flush_agg(const Params &p, Agg a, bool leader,
     }
 }
 
-template <int G>
-__device__ __forceinline__ int next_cell(const Params &p, int g) {
-    if (!p.persistent) return p.n_cells;
-    int c = 0;
-    if (g == 0) c = atomicAdd(p.queue, 1);
-    c = __shfl(c, 0, G);
-    return p.groups_total + c;
+// Claims on the work queue by groups of G lanes (64: one claim per wave; the
+// NW waves that share a cell claim together).  A group claims from its own part
+// until that is used up, then from the next; a part seen or claimed past its
+// end is never asked again.
+template <int G, int NW = 1>
+struct Claim {
+    int part, left;
+
+    __device__ __forceinline__ void init() {
+        part = __builtin_amdgcn_readfirstlane(
+            (int)((blockIdx.x + threadIdx.x / (64 * NW)) % QUEUE_PARTS));
+        left = QUEUE_PARTS;
+    }
+    // unsigned: heads run past the end of the largest launches
+    __device__ __forceinline__ unsigned position(const Params &p, int i) const {
+        return (unsigned)(p.groups_total + part) + (unsigned)i * QUEUE_PARTS;
+    }
+    // the next position of the queue; n_cells once every part is used up
+    __device__ __forceinline__ int next(const Params &p, int g) {
+        while (left > 0) {
+            int i = 0;
+            if (g == 0) i = atomicAdd(p.queue + part * QUEUE_STRIDE, 1);
+            const unsigned pos = position(p, __shfl(i, 0, G));
+            if (pos < (unsigned)p.n_cells) return (int)pos;
+            do {
+                --left;
+                part = (part + 1) % QUEUE_PARTS;
+            } while (left > 0 &&
+                     position(p, __hip_atomic_load(p.queue + part * QUEUE_STRIDE, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT)) >= (unsigned)p.n_cells);
+        }
+        return p.n_cells;
+    }
+};
+
+// The cell at a queue position, -1 past the end.
+__device__ __forceinline__ int cell_at(const Params &p, int i) {
+    return i >= p.n_cells ? -1 : i;
 }
 
+// The state of a cell; false if T or P is not positive or any of it not finite.
 template <int G, int NSL>
 __device__ __forceinline__ bool load_state(const Params &p, int cell, int g, double (&y)[NSL],
                                            double &P10) {
@@ -227,11 +259,13 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
     S.agg = Agg{0, 0, 0, 0, 0, 0, 0, 0};
     S.invP10 = 1e-6;
 
-    // Take the next valid cell starting at `first` (cells with bad input are
-    // marked and skipped); S.cell = -1 when the queue is exhausted.
+    // Take the next valid cell starting at queue position `first` (cells with
+    // bad input are marked and skipped); S.cell = -1 when the queue is exhausted.
+    Claim<G> claim;
+    claim.init();
+    auto next_position = [&]() { return p.persistent ? claim.next(p, g) : p.n_cells; };
     auto acquire = [&](int first) {
-        int cell = first;
-        while (cell < p.n_cells) {
+        for (int cell = cell_at(p, first); cell >= 0; cell = cell_at(p, next_position())) {
             double P10;
             if (load_state<G, NSL>(p, cell, g, y, P10)) {
                 S.cell = cell;
@@ -248,7 +282,6 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
             Counts zc{0, 0, 0, 0, 0, 0, 0};
             store_counts(p, cell, g, zc, ST_BADINPUT);
             agg_cell(S.agg, zc, ST_BADINPUT);
-            cell = next_cell<G>(p, g);
         }
         S.cell = -1;
     };
@@ -540,7 +573,7 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
                 store_state<G, NSL>(p, S.cell, g, y);
                 store_counts(p, S.cell, g, c, fin);
                 agg_cell(S.agg, c, fin);
-                acquire(next_cell<G>(p, g));
+                acquire(next_position());
             }
         }
     }
@@ -598,9 +631,11 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
     S.agg = Agg{0, 0, 0, 0, 0, 0, 0, 0};
     S.invP10 = 1e-6;
 
+    Claim<G> claim;
+    claim.init();
+    auto next_position = [&]() { return p.persistent ? claim.next(p, g) : p.n_cells; };
     auto acquire = [&](int first) {
-        int cell = first;
-        while (cell < p.n_cells) {
+        for (int cell = cell_at(p, first); cell >= 0; cell = cell_at(p, next_position())) {
             double P10;
             if (load_state<G, NSL>(p, cell, g, y, P10)) {
                 S.cell = cell;
@@ -619,7 +654,6 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
             Counts zc{0, 0, 0, 0, 0, 0, 0};
             store_counts(p, cell, g, zc, ST_BADINPUT);
             agg_cell(S.agg, zc, ST_BADINPUT);
-            cell = next_cell<G>(p, g);
         }
         S.cell = -1;
     };
@@ -736,7 +770,7 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
                 store_state<G, NSL>(p, S.cell, g, y);
                 store_counts(p, S.cell, g, c, fin);
                 agg_cell(S.agg, c, fin);
-                acquire(next_cell<G>(p, g));
+                acquire(next_position());
             }
         }
     }

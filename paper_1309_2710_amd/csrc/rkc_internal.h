@@ -65,7 +65,7 @@ int check_integrate_args(double dt, double rtol, double atol, const rkc_opts &o)
 
 // Enqueue one integration of n cells whose arrays are device pointers on the
 // mechanism's device, with the launch's own scratch (aggregate counters
-// [16], work-queue head): launches that use distinct scratch may run
+// [16], work-queue heads): launches that use distinct scratch may run
 // concurrently on different streams.  Not thread-safe for one mechanism
 // (its per-shape table cache is filled on first use).  With may_build false
 // nothing is allocated: RKC_ENOTSUP if the tables of the selected variant

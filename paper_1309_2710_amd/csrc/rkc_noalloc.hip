@@ -1,6 +1,6 @@
 // rkc_integrate_device_noalloc (include/rkc.h): rkc_integrate with device
 // arrays whose launch scratch -- the aggregate counters and the work-queue
-// head that the integrator kernels update -- is a file-scope device array
+// heads that the integrator kernels update -- is a file-scope device array
 // instead of memory owned by the mechanism handle, and which allocates
 // nothing.
 #include <atomic>
@@ -11,11 +11,9 @@
 
 namespace {
 
-// Scratch of one launch: AGG_N aggregate counters, then the work-queue head
-// (an int in the next 8-byte word); the rest is spare.  Every device the
-// library runs on holds its own copy until the process ends.
-constexpr int SCRATCH_WORDS = 32;
-static_assert(rkchost::AGG_N + 1 <= SCRATCH_WORDS, "scratch too small");
+// Scratch of one launch: AGG_N aggregate counters, then the work-queue heads.
+// Every device the library runs on holds its own copy until the process ends.
+constexpr int SCRATCH_WORDS = rkchost::AGG_N + rkcdev::QUEUE_INTS / 2;
 static __device__ __align__(256) unsigned long long scratch[SCRATCH_WORDS];
 
 // Device address of `scratch` on each device, resolved on the first call with

@@ -202,7 +202,7 @@ int rkc_server_create(const rkc_server_opts *opts, rkc_server **out) {
             hipEventCreateWithFlags(&sl.ev, hipEventDisableTiming) != hipSuccess)
             rc = RKC_EDEVICE;
         else if (hipMalloc(&sl.agg_d, rkchost::AGG_N * 8) != hipSuccess ||
-                 hipMalloc(&sl.queue_d, sizeof(int)) != hipSuccess ||
+                 hipMalloc(&sl.queue_d, rkcdev::QUEUE_INTS * sizeof(int)) != hipSuccess ||
                  hipHostMalloc(&sl.agg_h, rkchost::AGG_N * 8, hipHostMallocDefault) != hipSuccess)
             rc = RKC_ENOMEM;
     }

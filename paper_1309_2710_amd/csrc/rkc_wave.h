@@ -483,26 +483,27 @@ __device__ __forceinline__ double floor_sqrt(double x) {
     return d > 0.0 ? k - 1.0 : k;
 }
 
-// The next cell of the launch for the wave (for NW > 1: for the workgroup).
+// The cell that follows in the queue, the same in every wave of the cell.
 template <int NW>
-__device__ __forceinline__ int wave_next(const Params &p, WaveState &S0, int l) {
-    if (!p.persistent) return p.n_cells;
+__device__ __forceinline__ int wave_next(const Params &p, Claim<64, NW> &claim, WaveState &S0, int l) {
+    if (!p.persistent) return -1;
     if constexpr (NW == 1) {
-        int c = 0;
-        if (l == 0) c = atomicAdd(p.queue, 1);
-        return p.groups_total + uni(c);
+        return uni(cell_at(p, claim.next(p, l)));
     } else {
         __syncthreads();
-        if (l == 0) S0.slot = atomicAdd(p.queue, 1);
+        if (l < 64) {
+            const int pos = claim.next(p, l);
+            if (l == 0) S0.slot = pos;
+        }
         __syncthreads();
-        return p.groups_total + uni(S0.slot);
+        return uni(cell_at(p, S0.slot));
     }
 }
 
 template <int SG, int NSL>
 __device__ __forceinline__ bool wave_load(const Params &p, int cell, int g, double (&y)[NSL],
                                           double &P10) {
-    int bad = 0;
+    bool bad = false;
 #pragma unroll
     for (int s = 0; s < NSL; ++s) {
         const int k = s * SG + g;
@@ -518,7 +519,7 @@ __device__ __forceinline__ bool wave_load(const Params &p, int cell, int g, doub
     }
     const double P = opaque_vd(p.P[cell]);
     bad |= !(P > 0.0) || !isfinite(P);
-    P10 = P * 10.0;
+    P10 = opaque_vd(P * 10.0);
     return !any(bad);
 }
 
@@ -593,11 +594,13 @@ __global__ RKC_WAVE_BOUNDS void rkc_wave_kernel(Params p) {
     RKC_WAVE_PROLOGUE
     const double sqrt_u = sqrt(u_round);
     const int coef_smax = p.coef_smax;
-    int cell = uni((int)blockIdx.x * (int)(blockDim.x / LANES) + (int)(threadIdx.x / LANES));
-    for (; cell < p.n_cells; cell = wave_next<NW>(p, *L.state0, l)) {
+    Claim<64, NW> claim;
+    claim.init();
+    int cell = uni(cell_at(p, (int)(blockIdx.x * (blockDim.x / LANES) + threadIdx.x / LANES)));
+    for (; cell >= 0; cell = wave_next<NW>(p, claim, *L.state0, l)) {
         double y[NSL], f0[NSL], z[NSL], fz[NSL], v[NSL];
-        double P10;
         Counts c{0, 0, 0, 0, 0, 0, 0};
+        double P10;
         if (!wave_load<SG, NSL>(p, cell, g, y, P10)) {
             if (l == 0) { store_counts(p, cell, 0, c, ST_BADINPUT); agg_cell(S.agg, c, ST_BADINPUT); }
             continue;
@@ -829,11 +832,13 @@ __global__ RKC_WAVE_BOUNDS void rkc_wave_kernel(Params p) {
 RKC_WAVE_TEMPLATE
 __global__ RKC_WAVE_BOUNDS void rkck_wave_kernel(Params p) {
     RKC_WAVE_PROLOGUE
-    int cell = uni((int)blockIdx.x * (int)(blockDim.x / LANES) + (int)(threadIdx.x / LANES));
-    for (; cell < p.n_cells; cell = wave_next<NW>(p, *L.state0, l)) {
+    Claim<64, NW> claim;
+    claim.init();
+    int cell = uni(cell_at(p, (int)(blockIdx.x * (blockDim.x / LANES) + threadIdx.x / LANES)));
+    for (; cell >= 0; cell = wave_next<NW>(p, claim, *L.state0, l)) {
         double y[NSL];
-        double P10;
         Counts c{0, 0, 0, 0, 0, 0, 0};
+        double P10;
         if (!wave_load<SG, NSL>(p, cell, g, y, P10)) {
             if (l == 0) { store_counts(p, cell, 0, c, ST_BADINPUT); agg_cell(S.agg, c, ST_BADINPUT); }
             continue;
