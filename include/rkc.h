@@ -28,7 +28,7 @@
  *   - units: T in K, P in Pa, Y mass fractions, dt in s; mechanism units are
  *     listed at rkc_mech_desc.
  *   - calls that share one rkc_mech handle must not overlap in time (they share
- *     the handle's device scratch: work queue and statistics).
+ *     the handle's device scratch: work queue, its order and statistics).
  */
 #ifndef RKC_H
 #define RKC_H
@@ -66,9 +66,11 @@ extern "C" {
                                     RKC_SCHED_PERSISTENT, or _PLAIN when every cell is
                                     resident */
 #define RKC_SCHED_PLAIN       1  /* one lane group per cell, grid covers all cells */
-#define RKC_SCHED_PERSISTENT  2  /* resident grid; groups pull cells from a device queue
-                                    in index order (cells ordered by decreasing expected
-                                    cost, e.g. temperature, shorten the final tail) */
+#define RKC_SCHED_PERSISTENT  2  /* resident grid; groups pull cells from a device queue,
+                                    those of the largest expected cost first (in index
+                                    order in served and no-allocation launches, in
+                                    launches that a caller captures, and past 2^22
+                                    cells) */
 
 /* ---- placement of reaction parameters (never changes results) --------- */
 #define RKC_PARAMS_AUTO       0  /* LDS (the measured faster placement), or global

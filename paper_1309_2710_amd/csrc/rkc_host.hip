@@ -48,6 +48,7 @@ struct rkc_graph {
     hipGraphExec_t exec = nullptr;
     unsigned long long *agg_d = nullptr;
     int *queue_d = nullptr;
+    rkchost::OrderScratch order;
 };
 
 struct rkc_mech {
@@ -69,6 +70,7 @@ struct rkc_mech {
     int *queue_d = nullptr;
     void *stage_d = nullptr;
     size_t stage_bytes = 0;
+    rkchost::OrderScratch order;                       // of rkc_integrate calls
     int num_cus = 0;
     size_t max_lds = 0;
     // tables of the one-lane-per-cell kernels (built on first use)
@@ -612,11 +614,57 @@ int ensure_stage(rkc_mech *m, size_t bytes) {
     return RKC_OK;
 }
 
-__global__ void reset_scratch_kernel(unsigned long long *agg, int *queue) {
+__global__ void reset_scratch_kernel(unsigned long long *agg, int *queue, unsigned *hist) {
     if (threadIdx.x < AGG_N) agg[threadIdx.x] = 0ull;
     for (int i = threadIdx.x; i < rkcdev::QUEUE_INTS; i += blockDim.x) queue[i] = 0;
+    if (hist)
+        for (int i = threadIdx.x; i < 2 * rkcdev::ORDER_BINS; i += blockDim.x) hist[i] = 0u;
 }
 
+// Queue order from the cells' cost classes: a counting sort, largest class
+// first (within a class in no fixed order, which no result depends on).
+// hist[0..BINS) holds the class counts, hist[BINS..2 BINS) the places handed
+// out so far.  Each workgroup ranks its cells in LDS and takes one range per
+// class.
+constexpr int ORDER_THREADS = 1024, ORDER_PER_THREAD = 4;
+__global__ __launch_bounds__(ORDER_THREADS) void order_kernel(const uint16_t *key, unsigned *hist,
+                                                              int n, int *order) {
+    constexpr int BINS = rkcdev::ORDER_BINS;
+    __shared__ unsigned place[BINS], count[BINS], part[ORDER_THREADS];
+    const int t = threadIdx.x;
+    // places of the classes: exclusive sums from the largest class down, two
+    // classes per thread
+    const unsigned c0 = hist[BINS - 1 - 2 * t], c1 = hist[BINS - 2 - 2 * t];
+    part[t] = c0 + c1;
+    count[2 * t] = 0u;
+    count[2 * t + 1] = 0u;
+    for (int d = 1; d < ORDER_THREADS; d *= 2) {
+        __syncthreads();
+        const unsigned v = t >= d ? part[t - d] : 0u;
+        __syncthreads();
+        part[t] += v;
+    }
+    place[BINS - 1 - 2 * t] = part[t] - c0 - c1;
+    place[BINS - 2 - 2 * t] = part[t] - c1;
+    __syncthreads();
+    const int base = blockIdx.x * (ORDER_THREADS * ORDER_PER_THREAD) + t;
+    unsigned k[ORDER_PER_THREAD], rank[ORDER_PER_THREAD];
+#pragma unroll
+    for (int i = 0; i < ORDER_PER_THREAD; ++i) {
+        const int c = base + i * ORDER_THREADS;
+        k[i] = c < n ? key[c] : 0u;
+        if (c < n) rank[i] = atomicAdd(&count[k[i]], 1u);
+    }
+    __syncthreads();
+    for (int b = t; b < BINS; b += ORDER_THREADS)
+        if (count[b]) place[b] += atomicAdd(hist + BINS + b, count[b]);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < ORDER_PER_THREAD; ++i) {
+        const int c = base + i * ORDER_THREADS;
+        if (c < n) order[place[k[i]] + rank[i]] = c;
+    }
+}
 
 struct Launch {
     int threads, blocks, groups_per_block;
@@ -773,9 +821,9 @@ int plan_wave_launch(const rkc_mech *m, const rkchost::WaveDesc &d, const NkTabl
 // Source-term launch of the lane-group variants: a grid that covers the chip
 // once (the kernel walks over the cells), in smaller workgroups while there are
 // too few cells to reach every compute unit, but with 512 lanes to stage the
-// tables.
+// tables; extra bytes of LDS follow the workgroup's own.
 int plan_rhs_launch(const rkc_mech *m, const Choice &ch, const NkTables *nk, const void *kernel,
-                    size_t n, const rkc_opts &o, Launch *L) {
+                    size_t n, const rkc_opts &o, size_t extra, Launch *L) {
     const int G = ch.v.G;
     const rkcdev::Shape sh = shape_for(ch, nk);
     int gpb = std::max(1, ch.v.max_threads / G);
@@ -784,10 +832,10 @@ int plan_rhs_launch(const rkc_mech *m, const Choice &ch, const NkTables *nk, con
     } else {
         while (gpb * G > 512 && (size_t)gpb * (size_t)m->num_cus > n) gpb = (gpb + 1) / 2;
     }
-    while (gpb > 1 && rkcdev::lds_bytes(sh, gpb) > m->max_lds) --gpb;
+    while (gpb > 1 && rkcdev::lds_bytes(sh, gpb) + extra > m->max_lds) --gpb;
     L->groups_per_block = gpb;
     L->threads = gpb * G;
-    L->lds = rkcdev::lds_bytes(sh, gpb);
+    L->lds = rkcdev::lds_bytes(sh, gpb) + extra;
     if (L->lds > m->max_lds) return RKC_ENOTSUP;
     HIP_OK(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L->lds));
     int per_cu = 0;
@@ -797,6 +845,10 @@ int plan_rhs_launch(const rkc_mech *m, const Choice &ch, const NkTables *nk, con
     L->persistent = false;
     return RKC_OK;
 }
+
+// Cells of a launch worth ordering: beyond this the queue's tail is under a
+// percent of the launch.
+constexpr size_t ORDER_MAX_CELLS = (size_t)1 << 22;
 
 void fill_params(const rkc_mech *m, const Choice &ch, const NkTables *nk, rkcdev::Params *p) {
     std::memset(p, 0, sizeof(*p));
@@ -892,7 +944,7 @@ int check_integrate_args(double dt, double rtol, double atol, const rkc_opts &o)
 int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, double *Yd, double dt,
                       double rtol, double atol, const rkc_opts &o, int32_t *sd, int32_t *cd,
                       unsigned long long *agg_d, int *queue_d, hipStream_t st, LaunchInfo *li,
-                      bool may_build) {
+                      bool may_build, OrderScratch *ord) {
     Choice ch;
     NkTables *nk = nullptr;
     int rc = select_variant(m, o, &ch, &nk, may_build);
@@ -913,10 +965,21 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
     // launch errors are taken from the launch call itself: the thread's last
     // error can hold an unrelated earlier status (e.g. a not-ready query made
     // by other code in the process)
+    // Cells that queue are taken in order of their expected cost: one evaluation
+    // per cell and a sort (0.3 ms for 262,144 cells of 13 species) against a tail
+    // of the longest cells, started last by chance.  In index order / ordered, ms:
+    // 9 species RKCK 262,144 cells 15.9 / 12.5; 13 species RKC 262,144 25.7 / 21.2;
+    // 53 species falloff 16,411 29.5 / 25.7; 53 species 131,072 130.7 / 129.0;
+    // 111 species 8,192 74.3 / 66.6; 13 species RKCK 262,144 (10 evaluations a
+    // cell) 1.06 / 1.10.  Not when every cell is resident: nothing queues.
+    const bool ordered = ord && L.persistent && ch.v.G > 1 && n <= ORDER_MAX_CELLS &&
+                         n > (size_t)L.blocks * (size_t)L.groups_per_block &&
+                         reserve_order(ord, n, may_build);
     {
-        void *rargs[] = {&agg_d, &queue_d};
+        unsigned *hist = ordered ? ord->hist : nullptr;
+        void *rargs[] = {&agg_d, &queue_d, &hist};
         HIP_OK(hipLaunchKernel(reinterpret_cast<const void *>(&reset_scratch_kernel), dim3(1),
-                               dim3(512), rargs, 0, st));
+                               dim3(ordered ? 1024 : 512), rargs, 0, st));
     }
     rkcdev::Params p;
     fill_params(m, ch, nk, &p);
@@ -941,6 +1004,23 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
         p.yss = (long long)n;
     }
     void *args[] = {&p};
+    if (ordered) {
+        const void *krhs = pd ? ch.v.k_rhs_pd : ch.v.k_rhs;
+        Launch K;
+        rc = plan_rhs_launch(m, ch, nk, krhs, n, rkc_opts{}, 4 * rkcdev::ORDER_BINS, &K);
+        if (rc) return rc;
+        p.key = ord->key;
+        p.hist = ord->hist;
+        HIP_OK(hipLaunchKernel(krhs, dim3(K.blocks), dim3(K.threads), args, K.lds, st));
+        int n_a = (int)n;
+        void *oargs[] = {&ord->key, &ord->hist, &n_a, &ord->order};
+        const int per = ORDER_THREADS * ORDER_PER_THREAD;
+        HIP_OK(hipLaunchKernel(reinterpret_cast<const void *>(&order_kernel),
+                               dim3((unsigned)((n + per - 1) / per)), dim3(ORDER_THREADS), oargs, 0,
+                               st));
+        p.key = nullptr;
+        p.order = ord->order;
+    }
     HIP_OK(hipLaunchKernel(kernel, dim3(L.blocks), dim3(L.threads), args, L.lds, st));
     li->G = ch.v.G;
     li->RUC = !wd ? ch.v.RUC
@@ -950,6 +1030,33 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
     li->threads = L.threads;
     li->lds = L.lds;
     return RKC_OK;
+}
+
+void free_order(OrderScratch *s) {
+    if (s->order) (void)hipFree(s->order);
+    if (s->key) (void)hipFree(s->key);
+    if (s->hist) (void)hipFree(s->hist);
+    *s = OrderScratch{};
+}
+
+bool reserve_order(OrderScratch *s, size_t n, bool may_build) {
+    if (s->cap >= n) return true;
+    if (!may_build) return false;
+    const size_t cap = std::min(ORDER_MAX_CELLS, std::max((n + 4095) / 4096 * 4096, 2 * s->cap));
+    // not counted against a capture that another thread may have under way
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    free_order(s);   // waits for the launches that use it
+    if (hipMalloc(&s->order, cap * sizeof(int)) == hipSuccess &&
+        hipMalloc(&s->key, cap * sizeof(uint16_t)) == hipSuccess &&
+        hipMalloc(&s->hist, 2 * rkcdev::ORDER_BINS * sizeof(unsigned)) == hipSuccess) {
+        s->cap = cap;
+    } else {
+        (void)hipGetLastError();
+        free_order(s);   // the queue then runs in index order
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return s->cap >= n;
 }
 
 int prepare(rkc_mech *m, const rkc_opts &o, size_t n_cells) {
@@ -1040,6 +1147,7 @@ int rkc_mech_destroy(rkc_mech *m) {
     if (m->coef_d) (void)hipFree(m->coef_d);
     if (m->pdep_d) (void)hipFree(m->pdep_d);
     if (m->stage_d) (void)hipFree(m->stage_d);
+    rkchost::free_order(&m->order);
     if (m->l_spec_d) (void)hipFree(m->l_spec_d);
     if (m->l_units_d) (void)hipFree(m->l_units_d);
     if (m->l_eff_d) (void)hipFree(m->l_eff_d);
@@ -1334,7 +1442,7 @@ int rkc_rhs(const rkc_mech *mc, size_t n, const double *T, const double *P, cons
     const void *krhs = m->n_pdep > 0 ? ch.v.k_rhs_pd : ch.v.k_rhs;
     if (!krhs) return RKC_ENOTSUP;
     rc = ch.v.G == 1 ? plan_launch(m, ch, krhs, n, lo, false, nk, &L)
-                     : plan_rhs_launch(m, ch, nk, krhs, n, lo, &L);
+                     : plan_rhs_launch(m, ch, nk, krhs, n, lo, 0, &L);
     if (rc) return rc;
     rkcdev::Params p;
     fill_params(m, ch, nk, &p);
@@ -1397,8 +1505,14 @@ int rkc_integrate(const rkc_mech *mc, size_t n, double *T, const double *P, doub
         Pd = Pb;
     }
     rkchost::LaunchInfo li;
+    // a caller's own capture would keep the order scratch's address past its
+    // next growth: such a launch takes its cells in index order
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool capturing = hipStreamIsCapturing(st, &cap) != hipSuccess ||
+                           cap != hipStreamCaptureStatusNone;
+    if (capturing) (void)hipGetLastError();
     rc = rkchost::enqueue_integrate(m, n, Td, Pd, Yd, dt, rtol, atol, o, sd, cd, m->agg_d,
-                                    m->queue_d, st, &li);
+                                    m->queue_d, st, &li, true, capturing ? nullptr : &m->order);
     if (rc) return rc;
     unsigned long long agg[AGG_N] = {0};
     const bool sync = !o.device_ptrs || stats;
@@ -1472,6 +1586,7 @@ int rkc_graph_destroy(rkc_graph *g) {
     if (g->graph) (void)hipGraphDestroy(g->graph);
     if (g->agg_d) (void)hipFree(g->agg_d);
     if (g->queue_d) (void)hipFree(g->queue_d);
+    rkchost::free_order(&g->order);
     (void)hipSetDevice(dev);
     delete g;
     return RKC_OK;
@@ -1500,6 +1615,7 @@ int rkc_graph_create(const rkc_mech *mc, size_t n, double *T, const double *P, d
         hipMalloc(&g->queue_d, rkcdev::QUEUE_INTS * sizeof(int)) != hipSuccess)
         rc = RKC_ENOMEM;
     if (rc == RKC_OK) rc = rkchost::prepare(m, o, n);
+    if (rc == RKC_OK && n <= ORDER_MAX_CELLS) (void)rkchost::reserve_order(&g->order, n, true);
     if (rc == RKC_OK &&
         hip_failed(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking), "hipStreamCreate",
                    __LINE__))
@@ -1511,7 +1627,7 @@ int rkc_graph_create(const rkc_mech *mc, size_t n, double *T, const double *P, d
     if (rc == RKC_OK) {
         const int erc = rkchost::enqueue_integrate(m, n, T, P, Y, dt, rtol, atol, o, cell_status,
                                                    o.cell_counters, g->agg_d, g->queue_d, cap,
-                                                   &li);
+                                                   &li, false, &g->order);
         const bool end_bad = hip_failed(hipStreamEndCapture(cap, &g->graph), "EndCapture",
                                         __LINE__);
         rc = erc ? erc : (end_bad ? RKC_EDEVICE : RKC_OK);
@@ -1593,7 +1709,8 @@ int rkc_autotune(const rkc_mech *mc, size_t n, const double *T, const double *P,
                 hip_failed(hipEventRecord(e0, st), "record", __LINE__))
                 return RKC_EDEVICE;
             const int erc = rkchost::enqueue_integrate(m, n, Tw, Pd, Yw, dt, rtol, atol, c, sd,
-                                                       nullptr, m->agg_d, m->queue_d, st, &li);
+                                                       nullptr, m->agg_d, m->queue_d, st, &li,
+                                                       true, &m->order);
             if (erc) return erc;
             float ms = 0.0f;
             if (hip_failed(hipEventRecord(e1, st), "record", __LINE__) ||

@@ -89,6 +89,8 @@ struct Claim {
     int part, left;
 
     __device__ __forceinline__ void init() {
+        // blocks and waves mixed: the first cells of waves with one number in
+        // their block are alike in an ordered queue
         part = __builtin_amdgcn_readfirstlane(
             (int)((blockIdx.x + threadIdx.x / (64 * NW)) % QUEUE_PARTS));
         left = QUEUE_PARTS;
@@ -117,7 +119,19 @@ struct Claim {
 
 // The cell at a queue position, -1 past the end.
 __device__ __forceinline__ int cell_at(const Params &p, int i) {
-    return i >= p.n_cells ? -1 : i;
+    if (i >= p.n_cells) return -1;
+    return p.order ? p.order[i] : i;
+}
+
+// Queue position of a group's first cell.  In an ordered queue neighbours are
+// alike, so the longest cells go to different workgroups, then to different
+// waves, before two share a wave; in index order a workgroup's cells are adjacent.
+template <int G>
+__device__ __forceinline__ int first_position(const Params &p, int groups, int gib) {
+    constexpr int GPW = 64 / G;
+    if (!p.order) return blockIdx.x * groups + gib;
+    const int spread = groups % GPW == 0 ? (gib % GPW) * (groups / GPW) + gib / GPW : gib;
+    return spread * (int)gridDim.x + (int)blockIdx.x;
 }
 
 // The state of a cell; false if T or P is not positive or any of it not finite.
@@ -286,7 +300,7 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
         S.cell = -1;
     };
 
-    acquire(blockIdx.x * groups + gib);
+    acquire(first_position<G>(p, groups, gib));
 
     unsigned iters = 0;
     for (;;) {
@@ -658,7 +672,7 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
         S.cell = -1;
     };
 
-    acquire(blockIdx.x * groups + gib);
+    acquire(first_position<G>(p, groups, gib));
 
     unsigned iters = 0;
     for (;;) {

@@ -63,17 +63,30 @@ namespace rkchost {
 // Validate the scalar arguments and options of an integration.
 int check_integrate_args(double dt, double rtol, double atol, const rkc_opts &o);
 
+// Scratch of a cost-ordered work queue: 6 bytes per cell and 16 KB, grown to
+// the largest launch (at most 2^22 cells are ordered) and kept by its owner.
+struct OrderScratch {
+    int *order = nullptr;
+    uint16_t *key = nullptr;
+    unsigned *hist = nullptr;
+    size_t cap = 0;
+};
+void free_order(OrderScratch *s);
+// Room for n cells; false if there is none and none may be or could be allocated.
+bool reserve_order(OrderScratch *s, size_t n, bool may_build);
+
 // Enqueue one integration of n cells whose arrays are device pointers on the
 // mechanism's device, with the launch's own scratch (aggregate counters
-// [16], work-queue heads): launches that use distinct scratch may run
+// [16], work-queue head): launches that use distinct scratch may run
 // concurrently on different streams.  Not thread-safe for one mechanism
 // (its per-shape table cache is filled on first use).  With may_build false
 // nothing is allocated: RKC_ENOTSUP if the tables of the selected variant
-// have not been built by an earlier call.
+// have not been built by an earlier call.  With `ord` the queue is ordered by
+// expected cost (not shared by launches that run concurrently).
 int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, double *Yd, double dt,
                       double rtol, double atol, const rkc_opts &o, int32_t *sd, int32_t *cd,
                       unsigned long long *agg_d, int *queue_d, hipStream_t st, LaunchInfo *li,
-                      bool may_build = true);
+                      bool may_build = true, OrderScratch *ord = nullptr);
 
 // Select the variant and build the device tables a later enqueue_integrate
 // with these options will use (so that concurrent launches only read them);

@@ -596,7 +596,7 @@ __global__ RKC_WAVE_BOUNDS void rkc_wave_kernel(Params p) {
     const int coef_smax = p.coef_smax;
     Claim<64, NW> claim;
     claim.init();
-    int cell = uni(cell_at(p, (int)(blockIdx.x * (blockDim.x / LANES) + threadIdx.x / LANES)));
+    int cell = uni(cell_at(p, first_position<64>(p, blockDim.x / LANES, threadIdx.x / LANES)));
     for (; cell >= 0; cell = wave_next<NW>(p, claim, *L.state0, l)) {
         double y[NSL], f0[NSL], z[NSL], fz[NSL], v[NSL];
         Counts c{0, 0, 0, 0, 0, 0, 0};
@@ -834,7 +834,7 @@ __global__ RKC_WAVE_BOUNDS void rkck_wave_kernel(Params p) {
     RKC_WAVE_PROLOGUE
     Claim<64, NW> claim;
     claim.init();
-    int cell = uni(cell_at(p, (int)(blockIdx.x * (blockDim.x / LANES) + threadIdx.x / LANES)));
+    int cell = uni(cell_at(p, first_position<64>(p, blockDim.x / LANES, threadIdx.x / LANES)));
     for (; cell >= 0; cell = wave_next<NW>(p, claim, *L.state0, l)) {
         double y[NSL];
         Counts c{0, 0, 0, 0, 0, 0, 0};
