@@ -122,6 +122,8 @@ struct Params {
     const int *order;                // cell of each queue position, or null: in index order
     uint16_t *key;                   // rhs kernel: cost classes of the cells instead of F, and
     unsigned *hist;                  // their counts [ORDER_BINS]
+    double *tail;                    // records of handed-over cells (see TAIL_DOUBLES), or null
+    int tail_cap;                    // their number at most
     // element (cell, i) of Y is Y[cell * ycs + i * yss] and element (cell, k)
     // of F is F[cell * fcs + k * fss]: (n_species, 1) and (N, 1) for
     // cell-major arrays, (1, n_cells) for species-major (cell-fastest) ones
@@ -142,6 +144,16 @@ struct Params {
 // of 10 evaluations to 1.75 ms, now 1.06); 16 heads on lines of their own take
 // 0.7 ns, and 64 measured the same.
 constexpr int QUEUE_PARTS = 16, QUEUE_STRIDE = 32, QUEUE_INTS = QUEUE_PARTS * QUEUE_STRIDE;
+
+// Hand-over of a lane-group launch's last cells to the one-cell-per-wave form,
+// which runs a cell 3 times faster but fills the chip with a fifth of the cells:
+// once at most tail_cap cells are left in flight (the queue's parts count the
+// groups that found it empty) a cell with more than TAIL_EVALS evaluations to go,
+// extrapolated over the rest of the interval, stops at its next step.  Its record:
+// the step control (16 words), then y, f(y) and the power method's vector.  The
+// waves look at the counts every TAIL_POLL evaluations.
+constexpr int QUEUE_IDLE = 1, QUEUE_TAIL = 2;   // ints of a part's line after its head
+constexpr int TAIL_DOUBLES = 64, TAIL_POLL = 64, TAIL_EVALS = 50;
 
 // Cost classes of the ordered work queue: the top 11 bits of a positive float.
 constexpr int ORDER_BINS = 2048;

@@ -769,9 +769,9 @@ int plan_launch(const rkc_mech *m, const Choice &ch, const void *kernel, size_t 
 //   53 species, falloff    1,031 13.7 / 6.1        16,411 29.6 / 34.3
 //   111 species            512 45 / 16              2,048 40 / 23     8,192 73.9 / 70
 const rkchost::WaveDesc *pick_wave(const rkc_mech *m, const Choice &ch, const NkTables *nk,
-                                   size_t n, double atol, const rkc_opts &o) {
-    if (!nk || o.schedule == RKC_SCHED_PLAIN || o.block_groups != 0 || o.grid_blocks != 0)
-        return nullptr;
+                                   size_t n, double atol, const rkc_opts &o, bool tail = false) {
+    if (!nk || o.schedule == RKC_SCHED_PLAIN) return nullptr;
+    if (!tail && (o.block_groups != 0 || o.grid_blocks != 0)) return nullptr;
     if (o.method == RKC_METHOD_RKC && atol < rkcdev::ATOL_WAVE) return nullptr;
     int cnt = 0;
     const rkchost::WaveDesc *t = rkchost::wave_variants(&cnt);
@@ -789,7 +789,8 @@ const rkchost::WaveDesc *pick_wave(const rkc_mech *m, const Choice &ch, const Nk
         if (rkcdev::wave_segments(nk->NSEG, d.SG, lanes) > d.MS || nk->SEGL > d.SL) continue;
         if (nk->L2P > d.LP || nk->L2N > d.LN) continue;
         const double resident = (double)(4 * d.occ / d.NW) * m->num_cus;
-        if (d.fill > 0.0 && (double)n > d.fill * resident) continue;
+        if (!tail && d.fill > 0.0 && (double)n > d.fill * resident) continue;
+        if (tail && !d.k_rkc_tail) continue;
         return &d;
     }
     return nullptr;
@@ -816,6 +817,12 @@ int plan_wave_launch(const rkc_mech *m, const rkchost::WaveDesc &d, const NkTabl
     L->persistent = o.schedule == RKC_SCHED_PERSISTENT || resident < all;
     L->blocks = (int)std::min(all, resident);
     return RKC_OK;
+}
+
+// Cells in flight at which a launch of lane groups hands them over: as many as
+// the wave form has resident.
+size_t tail_cells(const rkc_mech *m, const rkchost::WaveDesc &d) {
+    return (size_t)(4 * d.occ) * (size_t)m->num_cus;
 }
 
 // Source-term launch of the lane-group variants: a grid that covers the chip
@@ -1003,6 +1010,21 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
         p.ycs = 1;
         p.yss = (long long)n;
     }
+    // The lane groups' last cells go to the wave form, all its resident waves
+    // having one.
+    const rkchost::WaveDesc *td = wd || !ord ? nullptr : pick_wave(m, ch, nk, n, atol, o, true);
+    const void *tail_kernel = nullptr;
+    Launch W;
+    if (td) {
+        tail_kernel = o.method == RKC_METHOD_RKC ? td->k_rkc_tail : td->k_rkck_tail;
+        const size_t cap = tail_cells(m, *td);
+        rc = plan_wave_launch(m, *td, nk, tail_kernel, cap, rkc_opts{}, &W);
+        if (rc) return rc;
+        if (reserve_tail(ord, cap, may_build)) {
+            p.tail = ord->tail;
+            p.tail_cap = (int)cap;
+        }
+    }
     void *args[] = {&p};
     if (ordered) {
         const void *krhs = pd ? ch.v.k_rhs_pd : ch.v.k_rhs;
@@ -1022,6 +1044,8 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
         p.order = ord->order;
     }
     HIP_OK(hipLaunchKernel(kernel, dim3(L.blocks), dim3(L.threads), args, L.lds, st));
+    if (p.tail)
+        HIP_OK(hipLaunchKernel(tail_kernel, dim3(W.blocks), dim3(W.threads), args, W.lds, st));
     li->G = ch.v.G;
     li->RUC = !wd ? ch.v.RUC
                   : wd->UL == rkcdev::UNITS_REG ? 1 : (wd->UL == rkcdev::UNITS_LDS ? 0 : -1);
@@ -1032,11 +1056,35 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
     return RKC_OK;
 }
 
-void free_order(OrderScratch *s) {
+static void free_queue(OrderScratch *s) {
     if (s->order) (void)hipFree(s->order);
     if (s->key) (void)hipFree(s->key);
     if (s->hist) (void)hipFree(s->hist);
+    s->order = nullptr;
+    s->key = nullptr;
+    s->hist = nullptr;
+    s->cap = 0;
+}
+
+void free_order(OrderScratch *s) {
+    free_queue(s);
+    if (s->tail) (void)hipFree(s->tail);
     *s = OrderScratch{};
+}
+
+bool reserve_tail(OrderScratch *s, size_t cells, bool may_build) {
+    if (s->tail_cap >= cells) return true;
+    if (!may_build || s->tail) return false;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (hipMalloc(&s->tail, cells * rkcdev::TAIL_DOUBLES * sizeof(double)) == hipSuccess) {
+        s->tail_cap = cells;
+    } else {
+        (void)hipGetLastError();
+        s->tail = nullptr;
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return s->tail_cap >= cells;
 }
 
 bool reserve_order(OrderScratch *s, size_t n, bool may_build) {
@@ -1046,20 +1094,20 @@ bool reserve_order(OrderScratch *s, size_t n, bool may_build) {
     // not counted against a capture that another thread may have under way
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     (void)hipThreadExchangeStreamCaptureMode(&mode);
-    free_order(s);   // waits for the launches that use it
+    free_queue(s);   // waits for the launches that use it
     if (hipMalloc(&s->order, cap * sizeof(int)) == hipSuccess &&
         hipMalloc(&s->key, cap * sizeof(uint16_t)) == hipSuccess &&
         hipMalloc(&s->hist, 2 * rkcdev::ORDER_BINS * sizeof(unsigned)) == hipSuccess) {
         s->cap = cap;
     } else {
         (void)hipGetLastError();
-        free_order(s);   // the queue then runs in index order
+        free_queue(s);   // the queue then runs in index order
     }
     (void)hipThreadExchangeStreamCaptureMode(&mode);
     return s->cap >= n;
 }
 
-int prepare(rkc_mech *m, const rkc_opts &o, size_t n_cells) {
+int prepare(rkc_mech *m, const rkc_opts &o, size_t n_cells, OrderScratch *ord) {
     Choice ch;
     NkTables *nk = nullptr;
     int rc = select_variant(m, o, &ch, &nk);
@@ -1077,6 +1125,19 @@ int prepare(rkc_mech *m, const rkc_opts &o, size_t n_cells) {
             rc = plan_wave_launch(m, *wd, nk, k, n_cells, o, &L);
             if (rc) return rc;
         }
+    if (!ord) return RKC_OK;
+    if (n_cells <= ORDER_MAX_CELLS) (void)reserve_order(ord, n_cells, true);
+    if (ch.v.G > 1)
+        rc = plan_rhs_launch(m, ch, nk, pd ? ch.v.k_rhs_pd : ch.v.k_rhs, n_cells, rkc_opts{},
+                             4 * rkcdev::ORDER_BINS, &L);
+    if (rc) return rc;
+    if (const rkchost::WaveDesc *td = pick_wave(m, ch, nk, n_cells, 1.0, o, true)) {
+        (void)reserve_tail(ord, tail_cells(m, *td), true);
+        for (const void *k : {td->k_rkc_tail, td->k_rkck_tail}) {
+            rc = plan_wave_launch(m, *td, nk, k, tail_cells(m, *td), rkc_opts{}, &L);
+            if (rc) return rc;
+        }
+    }
     return RKC_OK;
 }
 
@@ -1614,8 +1675,7 @@ int rkc_graph_create(const rkc_mech *mc, size_t n, double *T, const double *P, d
     if (hipMalloc(&g->agg_d, AGG_N * sizeof(unsigned long long)) != hipSuccess ||
         hipMalloc(&g->queue_d, rkcdev::QUEUE_INTS * sizeof(int)) != hipSuccess)
         rc = RKC_ENOMEM;
-    if (rc == RKC_OK) rc = rkchost::prepare(m, o, n);
-    if (rc == RKC_OK && n <= ORDER_MAX_CELLS) (void)rkchost::reserve_order(&g->order, n, true);
+    if (rc == RKC_OK) rc = rkchost::prepare(m, o, n, &g->order);
     if (rc == RKC_OK &&
         hip_failed(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking), "hipStreamCreate",
                    __LINE__))

@@ -80,6 +80,19 @@ __device__ __forceinline__ void flush_agg(const Params &p, Agg a, bool leader,
     }
 }
 
+// The kernel's parameter block (the only kernel argument, at the start of
+// the kernarg segment) through a pointer the compiler cannot see through:
+// fields read through it are loaded with scalar loads where they are used,
+// instead of occupying scalar registers for the whole kernel.
+typedef const __attribute__((address_space(4))) Params ParamsK;
+__device__ __forceinline__ ParamsK *params_k() {
+    ParamsK *k = (ParamsK *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(k));
+    return k;
+}
+// The same by reference, for functions that take the launch's arguments.
+__device__ __forceinline__ const Params &params_now() { return *(const Params *)params_k(); }
+
 // Claims on the work queue by groups of G lanes (64: one claim per wave; the
 // NW waves that share a cell claim together).  A group claims from its own part
 // until that is used up, then from the next; a part seen or claimed past its
@@ -134,6 +147,43 @@ __device__ __forceinline__ int first_position(const Params &p, int groups, int g
     return spread * (int)gridDim.x + (int)blockIdx.x;
 }
 
+// Hand-over by lane groups: a group that finds the queue empty counts itself,
+// each wave looks at the counts now and then and sets its groups' `hands`.
+__device__ __forceinline__ void tail_idle(const Params &p, int g, int part) {
+    if (p.tail && g == 0) atomicAdd(p.queue + part * QUEUE_STRIDE + QUEUE_IDLE, 1);
+}
+
+// Where cells queue, a wave looks once one of its own groups is idle, and now
+// and then before: 4,096 waves reading the lines that the claims go to would hold
+// those up.
+__device__ __forceinline__ void tail_poll(const Params &p, unsigned iters, int cell, int &hands) {
+    if (p.persistent && !__any(cell < 0) && iters % 1024 != 0) return;
+    int n = __hip_atomic_load(p.queue + (threadIdx.x % QUEUE_PARTS) * QUEUE_STRIDE + QUEUE_IDLE,
+                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int m = 1; m < QUEUE_PARTS; m *= 2) n += __shfl_xor(n, m, 64);
+    hands = n > 0 && p.groups_total - n <= p.tail_cap;
+}
+
+// The slot of a cell that stops here, -1 if it goes on.
+template <int G>
+__device__ __forceinline__ int tail_slot(const Params &p, int g, const Counts &c, double t,
+                                         double t_end) {
+    if (!((double)c.n_rhs * (t_end - t) > TAIL_EVALS * t)) return -1;
+    int i = 0;
+    if (g == 0) i = atomicAdd(p.queue + QUEUE_TAIL, 1);
+    i = __shfl(i, 0, G);
+    return i < p.tail_cap ? i : -1;
+}
+
+// Step control of a handed-over cell; the RKCK machine uses h, t and flag.
+struct TailCell {
+    double h, t, sigma, h_prev, rprev;
+    int cell, need_sigma, since_sigma, flag;   // flag: predictive (RKC), last (RKCK)
+    Counts c;
+};
+static_assert(sizeof(TailCell) <= 16 * sizeof(double), "hand-over record");
+
 // The state of a cell; false if T or P is not positive or any of it not finite.
 template <int G, int NSL>
 __device__ __forceinline__ bool load_state(const Params &p, int cell, int g, double (&y)[NSL],
@@ -178,17 +228,6 @@ __device__ __forceinline__ void store_counts(const Params &p, int cell, int g, c
         o[0] = c.n_rhs; o[1] = c.n_steps; o[2] = c.n_reject; o[3] = c.n_sigma;
         o[4] = c.s_max_used; o[5] = c.s_hash; o[6] = status; o[7] = c.n_piter;
     }
-}
-
-// The kernel's parameter block (the only kernel argument, at the start of
-// the kernarg segment) through a pointer the compiler cannot see through:
-// fields read through it are loaded with scalar loads where they are used,
-// instead of occupying scalar registers for the whole kernel.
-typedef const __attribute__((address_space(4))) Params ParamsK;
-__device__ __forceinline__ ParamsK *params_k() {
-    ParamsK *k = (ParamsK *)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(k));
-    return k;
 }
 
 // Square of the weighted RMS norm (E:rmsE) over the N state components of
@@ -246,7 +285,7 @@ constexpr double NORM2_ACCEPT = 0x1.0000000000001p0;
 struct RkcState {
     double t, h, sigma, sigma_prev, delta, ht, h_prev, rprev, P10, invP10;
     double w0, w1, Tm1, Tm2, Tpm1, Tpm2, Tppm1, Tppm2, bm1, ibm1, ibm2;
-    int cell, phase, k_pow, s, j, last, need_sigma, since_sigma, predictive, after, tab;
+    int cell, phase, k_pow, s, j, last, need_sigma, since_sigma, predictive, after, tab, hands;
     Counts c;
     Agg agg;
 };
@@ -275,10 +314,13 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
 
     // Take the next valid cell starting at queue position `first` (cells with
     // bad input are marked and skipped); S.cell = -1 when the queue is exhausted.
+    constexpr bool HANDS = G == 16 && NSL == 1;   // variants with a wave form for the tail
+    S.hands = 0;
     Claim<G> claim;
     claim.init();
-    auto next_position = [&]() { return p.persistent ? claim.next(p, g) : p.n_cells; };
+    auto next_position = [&]() { const Params &p = params_now(); return p.persistent ? claim.next(p, g) : p.n_cells; };
     auto acquire = [&](int first) {
+        const Params &p = params_now();
         for (int cell = cell_at(p, first); cell >= 0; cell = cell_at(p, next_position())) {
             double P10;
             if (load_state<G, NSL>(p, cell, g, y, P10)) {
@@ -298,6 +340,7 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
             agg_cell(S.agg, zc, ST_BADINPUT);
         }
         S.cell = -1;
+        if constexpr (HANDS) tail_idle(p, g, claim.part);
     };
 
     acquire(first_position<G>(p, groups, gib));
@@ -306,6 +349,7 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
     for (;;) {
         if (!__any(S.cell >= 0)) break;   // a wave whose groups hold no cell issues nothing
         ++iters;
+        if (HANDS && iters % TAIL_POLL == 0) tail_poll(params_now(), iters, S.cell, S.hands);
         {
             ParamsK &pr = *params_k();
             rhs_eval<G, NSL, RUC, PD>(z, S.P10, S.invP10, fz, L, ur, g, N, pr.RU, pr.NSEG, pr.SEGL,
@@ -500,9 +544,24 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
             }
 
             if (act == ACT_BEGIN_STEP) {
+                int slot = -1;
                 if (c.n_steps + c.n_reject >= pk.max_steps) { act = ACT_FINISH; fin = ST_MAXSTEPS; }
+                else if (HANDS && S.hands && (slot = tail_slot<G>(params_now(), g, c, S.t, t_end)) >= 0) act = ACT_NONE;
                 else if (S.need_sigma) act = ACT_POWER_STEP;
                 else act = ACT_AFTER_SIGMA;
+                if constexpr (HANDS) {
+                    if (slot >= 0) {
+                        double *r = params_k()->tail + (long long)slot * TAIL_DOUBLES;
+                        if (g == 0)
+                            *reinterpret_cast<TailCell *>(r) =
+                                TailCell{S.h, S.t, S.sigma, S.h_prev, S.rprev, S.cell, S.need_sigma,
+                                         S.since_sigma, S.predictive, c};
+                        r[16 + g] = y[0];
+                        r[32 + g] = f0[0];
+                        r[48 + g] = v[0];
+                        S.cell = -1;
+                    }
+                }
             }
             if (act == ACT_POWER_INIT || act == ACT_POWER_STEP) {
                 double ny2 = 0.0, nv2 = 0.0;
@@ -584,6 +643,7 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
             }
             S.c = c;
             if (act == ACT_FINISH) {
+                const Params &p = params_now();
                 store_state<G, NSL>(p, S.cell, g, y);
                 store_counts(p, S.cell, g, c, fin);
                 agg_cell(S.agg, c, fin);
@@ -624,7 +684,7 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
 
 struct RkckState {
     double t, h, P10, invP10;
-    int cell, phase, last;
+    int cell, phase, last, hands;
     Counts c;
     Agg agg;
 };
@@ -645,10 +705,13 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
     S.agg = Agg{0, 0, 0, 0, 0, 0, 0, 0};
     S.invP10 = 1e-6;
 
+    constexpr bool HANDS = G == 16 && NSL == 1;   // variants with a wave form for the tail
+    S.hands = 0;
     Claim<G> claim;
     claim.init();
-    auto next_position = [&]() { return p.persistent ? claim.next(p, g) : p.n_cells; };
+    auto next_position = [&]() { const Params &p = params_now(); return p.persistent ? claim.next(p, g) : p.n_cells; };
     auto acquire = [&](int first) {
+        const Params &p = params_now();
         for (int cell = cell_at(p, first); cell >= 0; cell = cell_at(p, next_position())) {
             double P10;
             if (load_state<G, NSL>(p, cell, g, y, P10)) {
@@ -670,6 +733,7 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
             agg_cell(S.agg, zc, ST_BADINPUT);
         }
         S.cell = -1;
+        if constexpr (HANDS) tail_idle(p, g, claim.part);
     };
 
     acquire(first_position<G>(p, groups, gib));
@@ -678,9 +742,14 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
     for (;;) {
         if (!__any(S.cell >= 0)) break;   // a wave whose groups hold no cell issues nothing
         ++iters;
-        rhs_eval<G, NSL, RUC, PD>(z, S.P10, S.invP10, fz, L, ur, g, N, p.RU, p.NSEG, p.SEGL,
-                                  p.L2P, p.L2N, p.RUp, p.NMS, p.RU2, p.invTmax);
+        if (HANDS && iters % TAIL_POLL == 0) tail_poll(params_now(), iters, S.cell, S.hands);
+        {
+            ParamsK &pr = *params_k();
+            rhs_eval<G, NSL, RUC, PD>(z, S.P10, S.invP10, fz, L, ur, g, N, pr.RU, pr.NSEG, pr.SEGL,
+                                      pr.L2P, pr.L2N, pr.RUp, pr.NMS, pr.RU2, pr.invTmax);
+        }
         if (S.cell >= 0) {
+            ParamsK &pk = *params_k();
             Counts c = S.c;
             c.n_rhs += 1;
             const double h = S.h;
@@ -735,7 +804,7 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
                     const double del = CK_D1 * k1[i] + 0.0 * k2[i] + CK_D3 * k3[i] + CK_D4 * k4[i]
                                      + CK_D5 * k5[i] + CK_D6 * k6;
                     if (i * G + g < N) {
-                        const double d0 = p.rtol * (fabs(y[i]) + fabs(k1[i]) + 1e-30);
+                        const double d0 = pk.rtol * (fabs(y[i]) + fabs(k1[i]) + 1e-30);
                         const double r = fabs(del / d0);
                         if (!isfinite(r)) bad = 1;
                         else emax = fmax(emax, r);
@@ -765,7 +834,7 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
                 }
                 if (fin < 0) {
                     if (hn < h_min) fin = ST_UNDERFLOW;
-                    else if (c.n_steps + c.n_reject >= p.max_steps) fin = ST_MAXSTEPS;
+                    else if (c.n_steps + c.n_reject >= pk.max_steps) fin = ST_MAXSTEPS;
                     else {
                         const double t = S.t;
                         const int last = (hn >= t_end - t);
@@ -775,12 +844,24 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
 #pragma unroll
                         for (int i = 0; i < NSL; ++i) z[i] = y[i];
                         S.phase = CK_K1;
+                        if constexpr (HANDS) {
+                            const int slot = S.hands ? tail_slot<G>(params_now(), g, c, t, t_end) : -1;
+                            if (slot >= 0) {
+                                double *r = params_k()->tail + (long long)slot * TAIL_DOUBLES;
+                                if (g == 0)
+                                    *reinterpret_cast<TailCell *>(r) =
+                                        TailCell{hn, t, 0.0, 0.0, 0.0, S.cell, 0, 0, last, c};
+                                r[16 + g] = y[0];
+                                S.cell = -1;
+                            }
+                        }
                     }
                 }
             }
             }
             S.c = c;
             if (fin >= 0) {
+                const Params &p = params_now();
                 store_state<G, NSL>(p, S.cell, g, y);
                 store_counts(p, S.cell, g, c, fin);
                 agg_cell(S.agg, c, fin);

@@ -41,6 +41,7 @@ struct WaveDesc {
     bool pd;
     double fill;
     const void *k_rkc, *k_rkck;
+    const void *k_rkc_tail, *k_rkck_tail;   // for cells handed over by lane groups, or null
 };
 const WaveDesc *wave_variants(int *n);
 
@@ -64,14 +65,19 @@ namespace rkchost {
 int check_integrate_args(double dt, double rtol, double atol, const rkc_opts &o);
 
 // Scratch of a cost-ordered work queue: 6 bytes per cell and 16 KB, grown to
-// the largest launch (at most 2^22 cells are ordered) and kept by its owner.
+// the largest launch (at most 2^22 cells are ordered) and kept by its owner;
+// and the records of cells handed over to the wave form (512 bytes per resident
+// wave, 1.5 MB).
 struct OrderScratch {
     int *order = nullptr;
     uint16_t *key = nullptr;
     unsigned *hist = nullptr;
     size_t cap = 0;
+    double *tail = nullptr;
+    size_t tail_cap = 0;
 };
 void free_order(OrderScratch *s);
+bool reserve_tail(OrderScratch *s, size_t cells, bool may_build);
 // Room for n cells; false if there is none and none may be or could be allocated.
 bool reserve_order(OrderScratch *s, size_t n, bool may_build);
 
@@ -90,8 +96,9 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
 
 // Select the variant and build the device tables a later enqueue_integrate
 // with these options will use (so that concurrent launches only read them);
-// with n_cells > 0 also fix the kernels' launch attributes for that size.
-int prepare(rkc_mech *m, const rkc_opts &o, size_t n_cells);
+// with n_cells > 0 also fix the kernels' launch attributes for that size and,
+// with `ord`, reserve the queue's scratch.
+int prepare(rkc_mech *m, const rkc_opts &o, size_t n_cells, OrderScratch *ord = nullptr);
 int mech_species(const rkc_mech *m);
 int mech_device(const rkc_mech *m);
 

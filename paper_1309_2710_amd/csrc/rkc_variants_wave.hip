@@ -4,20 +4,29 @@
 #include "rkc_internal.h"
 #include "rkc_wave.h"
 
-#define RKC_WAVE_K(K_, PD_, ...)                                                                     \
-    reinterpret_cast<const void *>(&rkcdev::K_##_wave_kernel<__VA_ARGS__, PD_>)
+#define RKC_WAVE_K(K_, ...)                                                                          \
+    reinterpret_cast<const void *>(&rkcdev::K_##_wave_kernel<__VA_ARGS__>)
 
 #define RKC_WAVE(FILL_, OCC_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_)                         \
     rkchost::WaveDesc {                                                                              \
         SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, OCC_, false, FILL_,                           \
-            RKC_WAVE_K(rkc, false, OCC_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_),             \
-            RKC_WAVE_K(rkck, false, OCC_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_)             \
+            RKC_WAVE_K(rkc, OCC_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, false),             \
+            RKC_WAVE_K(rkck, OCC_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, false),            \
+            nullptr, nullptr                                                                         \
     }
 #define RKC_WAVE_PD(FILL_, OCC_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_)                      \
     rkchost::WaveDesc {                                                                              \
         SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, OCC_, true, FILL_,                            \
-            RKC_WAVE_K(rkc, true, OCC_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_),              \
-            RKC_WAVE_K(rkck, true, OCC_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_)              \
+            RKC_WAVE_K(rkc, OCC_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, true),              \
+            RKC_WAVE_K(rkck, OCC_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, true),             \
+            nullptr, nullptr                                                                         \
+    }
+// also with the kernels that finish the cells handed over by 16-lane groups
+#define RKC_WAVE_T(FILL_, PD_, ...)                                                                  \
+    rkchost::WaveDesc {                                                                              \
+        __VA_ARGS__, 3, PD_, FILL_, RKC_WAVE_K(rkc, 3, __VA_ARGS__, PD_),                            \
+            RKC_WAVE_K(rkck, 3, __VA_ARGS__, PD_), RKC_WAVE_K(rkc, 3, __VA_ARGS__, PD_, true),       \
+            RKC_WAVE_K(rkck, 3, __VA_ARGS__, PD_, true)                                              \
     }
 
 namespace rkchost {
@@ -25,9 +34,9 @@ namespace rkchost {
 // In order of preference: the first that fits the mechanism and the cell count
 // runs.  fill: the most cells per resident one (0: any number).
 static const WaveDesc kTable[] = {
-    RKC_WAVE(2.0, 3, 16, 1, 1, rkcdev::UNITS_REG, 1, 1, 8, 4, 2),
-    RKC_WAVE(2.0, 3, 16, 1, 1, rkcdev::UNITS_REG, 1, 1, 8, 4, 4),
-    RKC_WAVE_PD(2.0, 3, 16, 1, 1, rkcdev::UNITS_REG, 1, 1, 8, 4, 4),
+    RKC_WAVE_T(2.0, false, 16, 1, 1, rkcdev::UNITS_REG, 1, 1, 8, 4, 2),
+    RKC_WAVE_T(2.0, false, 16, 1, 1, rkcdev::UNITS_REG, 1, 1, 8, 4, 4),
+    RKC_WAVE_T(2.0, true, 16, 1, 1, rkcdev::UNITS_REG, 1, 1, 8, 4, 4),
     RKC_WAVE(1.125, 2, 64, 1, 3, rkcdev::UNITS_REG, 2, 2, 6, 8, 4),
     RKC_WAVE(0.0, 2, 64, 1, 5, rkcdev::UNITS_REG, 1, 4, 6, 8, 4),
     RKC_WAVE(0.0, 2, 64, 1, 5, rkcdev::UNITS_REG, 1, 3, 10, 8, 4),

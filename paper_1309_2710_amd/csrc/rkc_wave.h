@@ -544,6 +544,24 @@ __device__ __forceinline__ double4 wave_recurrence(WaveState &S) {
 #define RKC_WAVE_PROLOGUE                                                                    \
     extern __shared__ __align__(16) unsigned char lds_raw[];                                 \
     constexpr int LANES = 64 * NW;                                                           \
+    /* TAIL: the cells that the lane groups handed over, instead of a queue */               \
+    int n_tail = 0, at = (int)(threadIdx.x / LANES * gridDim.x + blockIdx.x);                \
+    if constexpr (TAIL) {                                                                    \
+        n_tail = min(p.queue[QUEUE_TAIL], p.tail_cap);                                       \
+        if ((int)blockIdx.x >= n_tail) return;                                               \
+    }                                                                                        \
+    unsigned long long done = 0;   /* evaluations of these cells before */                   \
+    const TailCell *rec = nullptr;                                                           \
+    auto tail_cell = [&]() {                                                                 \
+        if (at >= n_tail) return -1;                                                         \
+        rec = reinterpret_cast<const TailCell *>(p.tail + (long long)at * TAIL_DOUBLES);     \
+        at += (int)(blockDim.x / LANES * gridDim.x);                                         \
+        return uni(rec->cell);                                                               \
+    };                                                                                       \
+    auto first_cell = [&]() {                                                                \
+        if constexpr (TAIL) return tail_cell();                                              \
+        else return uni(cell_at(p, first_position<64>(p, blockDim.x / LANES, threadIdx.x / LANES))); \
+    };                                                                                       \
     WaveLds L;                                                                               \
     WaveTab<NSL, RUC, UL, MS, SL, LP, LN> w;                                                     \
     wave_setup<SG, NSL, RUC, UL, NW, MS, SL, LP, LN>(p, lds_raw, L, w);                          \
@@ -572,12 +590,13 @@ __device__ __forceinline__ double4 wave_recurrence(WaveState &S) {
     };
 
 #define RKC_WAVE_TEMPLATE                                                                    \
-    template <int OCC, int SG, int NSL, int RUC, int UL, int NW, int MS, int SL, int LP, int LN, bool PD>
+    template <int OCC, int SG, int NSL, int RUC, int UL, int NW, int MS, int SL, int LP, int LN, bool PD, bool TAIL = false>
 
 #define RKC_WAVE_BOUNDS __launch_bounds__((NW > 1 ? 64 * NW : 256 * OCC), OCC)
 
-// Totals of a wave's cells; every evaluation it issued advanced one.
-__device__ __forceinline__ void flush_wave(const Params &p, const Agg &a) {
+// Totals of a wave's cells; every evaluation it issued, all but `before` of
+// theirs, advanced one.
+__device__ __forceinline__ void flush_wave(const Params &p, const Agg &a, unsigned long long before) {
     atomicAdd(p.agg + 0, a.rhs);
     atomicAdd(p.agg + 1, a.steps);
     atomicAdd(p.agg + 2, a.rej);
@@ -586,7 +605,7 @@ __device__ __forceinline__ void flush_wave(const Params &p, const Agg &a) {
     atomicMax(p.agg + 5, (unsigned long long)a.smax);
     atomicAdd(p.agg + 6, (unsigned long long)a.failed);
     atomicMax(p.agg + 7, (unsigned long long)a.worst);
-    atomicAdd(p.agg + 8, a.rhs);
+    atomicAdd(p.agg + 8, a.rhs - before);
 }
 
 RKC_WAVE_TEMPLATE
@@ -596,12 +615,20 @@ __global__ RKC_WAVE_BOUNDS void rkc_wave_kernel(Params p) {
     const int coef_smax = p.coef_smax;
     Claim<64, NW> claim;
     claim.init();
-    int cell = uni(cell_at(p, first_position<64>(p, blockDim.x / LANES, threadIdx.x / LANES)));
-    for (; cell >= 0; cell = wave_next<NW>(p, claim, *L.state0, l)) {
+    auto next_cell = [&]() {
+        if constexpr (TAIL) return tail_cell();
+        else return wave_next<NW>(p, claim, *L.state0, l);
+    };
+    for (int cell = first_cell(); cell >= 0; cell = next_cell()) {
         double y[NSL], f0[NSL], z[NSL], fz[NSL], v[NSL];
         Counts c{0, 0, 0, 0, 0, 0, 0};
         double P10;
-        if (!wave_load<SG, NSL>(p, cell, g, y, P10)) {
+        if constexpr (TAIL) {
+            y[0] = reinterpret_cast<const double *>(rec)[16 + g];
+            c = rec->c;
+            done += (unsigned)c.n_rhs;
+            P10 = opaque_vd(p.P[cell] * 10.0);
+        } else if (!wave_load<SG, NSL>(p, cell, g, y, P10)) {
             if (l == 0) { store_counts(p, cell, 0, c, ST_BADINPUT); agg_cell(S.agg, c, ST_BADINPUT); }
             continue;
         }
@@ -612,6 +639,16 @@ __global__ RKC_WAVE_BOUNDS void rkc_wave_kernel(Params p) {
         bool initial = true, predictive = false;
 #pragma unroll
         for (int i = 0; i < NSL; ++i) z[i] = y[i];
+        if constexpr (TAIL) {
+            f0[0] = reinterpret_cast<const double *>(rec)[32 + g];
+            v[0] = reinterpret_cast<const double *>(rec)[48 + g];
+            h = opaque_vd(rec->h); t = opaque_vd(rec->t); sigma = opaque_vd(rec->sigma);
+            h_prev = opaque_vd(rec->h_prev); rprev = opaque_vd(rec->rprev);
+            need_sigma = uni(rec->need_sigma);
+            since_sigma = uni(rec->since_sigma);
+            predictive = uni(rec->flag) != 0;
+            initial = false;
+        }
         for (;;) {
             if (rare(need_sigma)) {
                 // spectral radius by the nonlinear power method; before the
@@ -826,7 +863,7 @@ __global__ RKC_WAVE_BOUNDS void rkc_wave_kernel(Params p) {
         if (l < SG) store_state<SG, NSL>(p, cell, g, y);
         if (l == 0) { store_counts(p, cell, 0, c, fin); agg_cell(S.agg, c, fin); }
     }
-    if (l == 0) flush_wave(p, S.agg);
+    if (l == 0) flush_wave(p, S.agg, done);
 }
 
 RKC_WAVE_TEMPLATE
@@ -834,12 +871,20 @@ __global__ RKC_WAVE_BOUNDS void rkck_wave_kernel(Params p) {
     RKC_WAVE_PROLOGUE
     Claim<64, NW> claim;
     claim.init();
-    int cell = uni(cell_at(p, first_position<64>(p, blockDim.x / LANES, threadIdx.x / LANES)));
-    for (; cell >= 0; cell = wave_next<NW>(p, claim, *L.state0, l)) {
+    auto next_cell = [&]() {
+        if constexpr (TAIL) return tail_cell();
+        else return wave_next<NW>(p, claim, *L.state0, l);
+    };
+    for (int cell = first_cell(); cell >= 0; cell = next_cell()) {
         double y[NSL];
         Counts c{0, 0, 0, 0, 0, 0, 0};
         double P10;
-        if (!wave_load<SG, NSL>(p, cell, g, y, P10)) {
+        if constexpr (TAIL) {
+            y[0] = reinterpret_cast<const double *>(rec)[16 + g];
+            c = rec->c;
+            done += (unsigned)c.n_rhs;
+            P10 = opaque_vd(p.P[cell] * 10.0);
+        } else if (!wave_load<SG, NSL>(p, cell, g, y, P10)) {
             if (l == 0) { store_counts(p, cell, 0, c, ST_BADINPUT); agg_cell(S.agg, c, ST_BADINPUT); }
             continue;
         }
@@ -849,6 +894,11 @@ __global__ RKC_WAVE_BOUNDS void rkck_wave_kernel(Params p) {
         t = 0.0;
         bool last = true;
         int fin;
+        if constexpr (TAIL) {
+            h = opaque_vd(rec->h);
+            t = opaque_vd(rec->t);
+            last = uni(rec->flag) != 0;
+        }
         for (;;) {
             double k1[NSL], k2[NSL], k3[NSL], k4[NSL], k5[NSL], z[NSL], fz[NSL];
             rhs(y, P10, invP10, fz);
@@ -923,7 +973,7 @@ __global__ RKC_WAVE_BOUNDS void rkck_wave_kernel(Params p) {
         if (l < SG) store_state<SG, NSL>(p, cell, g, y);
         if (l == 0) { store_counts(p, cell, 0, c, fin); agg_cell(S.agg, c, fin); }
     }
-    if (l == 0) flush_wave(p, S.agg);
+    if (l == 0) flush_wave(p, S.agg, done);
 }
 
 }  // namespace rkcdev

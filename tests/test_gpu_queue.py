@@ -20,7 +20,7 @@ def R():
 def _run(R, gm, st, dt, method, **kw):
     T, Y = st["T"].copy(), st["Y"].copy()
     out = R.integrate(gm, T, st["P"], Y, dt, 1e-6, 1e-10, method=method, counters=True, **kw)
-    return T, Y, out["counters"], out["status"]
+    return T, Y, out["counters"], out["status"], out.get("stats")
 
 
 # grids of 1, 3 and 17 workgroups of 1 or 3 lane groups: fewer cells than groups,
@@ -46,7 +46,7 @@ def test_queue_equals_plain(R, cfg, G, method, grid, groups, n):
     a = _run(R, gm, st, dt, method, lanes_per_cell=G, schedule=R.SCHED_PERSISTENT, grid_blocks=grid,
              block_groups=groups)
     b = _run(R, gm, st, dt, method, lanes_per_cell=G, schedule=R.SCHED_PLAIN, block_groups=groups)
-    for x, y in zip(a, b):
+    for x, y in zip(a[:4], b[:4]):
         assert np.array_equal(x, y, equal_nan=x.dtype == np.float64)
     if n > 3:
         assert (a[3][[0, 1, n - 1]] == 4).all()
@@ -84,3 +84,25 @@ def test_captured_call_and_graph_equal_eager(R, cfg, method):
         R.integrate(gm, Tb, P[r].contiguous(), Yb, dt, 1e-6, 1e-10, method=method, status=False)
         assert torch.equal(Tb, Te[r]) and torch.equal(Yb, Ye[r]), k
     graph.close()
+
+
+# 16-lane groups hand the cells they have left to one wave each: when every cell
+# was resident, when they queued, both methods, and steps whose stage counts or
+# error estimates take the rare branches
+@pytest.mark.parametrize("cfg,n,method,dt,kw", [
+    ("c1", 7000, 0, 3e-7, {}), ("c1", 20000, 1, 1e-8, {}), ("c2", 20001, 0, 1e-6, {}),
+    ("c2", 7001, 0, 1e-7, dict(stage_coefs=1)), ("c1", 7001, 0, 1e-6, dict(max_steps=40)),
+    ("c1", 7003, 0, 1e-6, dict(s_max=3)), ("c2", 7003, 0, 1e-6, dict(layout=1))])
+def test_handed_over_cells_equal_plain(R, cfg, n, method, dt, kw):
+    print("[case] hand-over", cfg, n, method, kw, flush=True)
+    st = synth.config_states(cfg, n, seed=n)
+    if kw.get("layout"):
+        st["Y"] = np.ascontiguousarray(st["Y"].T)
+    gm = R.Mechanism(synth.config_mechanism(cfg))
+    a = _run(R, gm, st, dt, method, stats=True, **kw)
+    b = _run(R, gm, st, dt, method, stats=True, schedule=R.SCHED_PLAIN, **kw)
+    for x, y in zip(a[:4], b[:4]):
+        assert np.array_equal(x, y)
+    for k in ("n_rhs", "n_steps", "n_reject", "n_sigma", "n_power_iter", "s_max_used", "n_failed"):
+        assert a[4][k] == b[4][k], k
+    assert a[4]["n_rhs"] <= a[4]["n_rhs_slots"] < b[4]["n_rhs_slots"]
