@@ -45,6 +45,13 @@ typedef __attribute__((address_space(3))) double lds_double;
 __device__ __forceinline__ uint32_t lds_addr(const void *p) {
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
 }
+// An address as a register of its own: otherwise the compiler keeps base and
+// offset apart and adds them at every read, 69 of the 427 vector instructions of
+// an evaluation of 53 species.
+__device__ __forceinline__ uint32_t opaque_vu(uint32_t a) {
+    asm("" : "+v"(a));
+    return a;
+}
 __device__ __forceinline__ double lds_at(uint32_t a) { return *(const lds_double *)(uintptr_t)a; }
 
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -222,8 +229,8 @@ __device__ __forceinline__ void wave_setup(const Params &p, unsigned char *lds_r
         }
 #pragma unroll
         for (int s = 0; s < 3; ++s) {
-            w.sf[r][s] = Ca + (used ? (uint32_t)((f >> (16 * s)) & 0xffffu) : 8u * p.nS);
-            w.sr[r][s] = Ca + (used ? (uint32_t)((v >> (16 * s)) & 0xffffu) : 8u * p.nS);
+            w.sf[r][s] = opaque_vu(Ca + (used ? (uint32_t)((f >> (16 * s)) & 0xffffu) : 8u * p.nS));
+            w.sr[r][s] = opaque_vu(Ca + (used ? (uint32_t)((v >> (16 * s)) & 0xffffu) : 8u * p.nS));
         }
     }
     // the gather tables of the SG-lane plan, chunk c = segment * SG + lane;
@@ -242,14 +249,14 @@ __device__ __forceinline__ void wave_setup(const Params &p, unsigned char *lds_r
 #pragma unroll
         for (int e = 0; e < SL; ++e) {
             const uint32_t y = (e & 1) ? (x[e / 2] >> 16) : (x[e / 2] & 0xffffu);
-            w.gt[m][e] = Qa + (used && e < p.SEGL && y != zt ? y : zt_w);
+            w.gt[m][e] = opaque_vu(Qa + (used && e < p.SEGL && y != zt ? y : zt_w));
         }
     }
     const int H2 = (p.L2P + p.L2N) / 2;
     auto piece_of = [&](int s, int i, bool used) {
         const uint32_t x = p.tab.gather2[(s * H2 + (used ? i / 2 : 0)) * SG + g];
         const uint32_t y = (i & 1) ? (x >> 16) : (x & 0xffffu);
-        return Pa + (used && y != zp ? y : zp_w);
+        return opaque_vu(Pa + (used && y != zp ? y : zp_w));
     };
 #pragma unroll
     for (int s = 0; s < NSL; ++s) {
@@ -261,10 +268,10 @@ __device__ __forceinline__ void wave_setup(const Params &p, unsigned char *lds_r
         w.W[s] = p.tab.spec[F_W * NK + k];
         w.invW[s] = p.tab.spec[F_INVW * NK + k];
         w.tmid[s] = p.tab.spec[F_TMID * NK + k];
-        w.cst[s] = Ca + 8u * (uint32_t)((k >= 1 && k < p.N && l < SG) ? k - 1 : NK);
+        w.cst[s] = opaque_vu(Ca + 8u * (uint32_t)((k >= 1 && k < p.N && l < SG) ? k - 1 : NK));
     }
-    w.qst = Qa + 8u * l;
-    w.pst = Pa + 8u * l;
+    w.qst = opaque_vu(Qa + 8u * l);
+    w.pst = opaque_vu(Pa + 8u * l);
     w.invTmax = opaque_vd(p.invTmax);
     __syncthreads();
 }
