@@ -272,7 +272,7 @@ int rkc_integrate(const rkc_mech *mech, size_t n_cells, double *T, const double 
  * rkc_integrate with device arrays (opts->device_ptrs must be 1, opts must not
  * be NULL) that calls no hipMalloc, hipFree or other allocating routine.  The
  * launch's scratch -- the aggregate counters and the work-queue heads of the
- * kernels, 2176 bytes -- is a file-scope device array of the library, one per
+ * kernels, 3200 bytes -- is a file-scope device array of the library, one per
  * GPU, cleared by a kernel at the start of every call; the call's size limit is
  * that of rkc_integrate (RKC_MAX_CELLS cells, RKC_ENOTSUP above).  Results are
  * those of rkc_integrate with the same options.  The mechanism's tables for the

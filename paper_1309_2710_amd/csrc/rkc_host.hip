@@ -1145,20 +1145,21 @@ int mech_species(const rkc_mech *m) { return m->nS; }
 int mech_device(const rkc_mech *m) { return m->device; }
 
 void fill_stats(const unsigned long long *agg, const LaunchInfo &li, rkc_stats *stats) {
+    constexpr int AS = rkcdev::AGG_STRIDE;
     stats->n_rhs = (int64_t)agg[0];
-    stats->n_steps = (int64_t)agg[1];
-    stats->n_reject = (int64_t)agg[2];
-    stats->n_sigma = (int64_t)agg[3];
-    stats->n_power_iter = (int64_t)agg[4];
-    stats->s_max_used = (int32_t)agg[5];
-    stats->n_failed = (int32_t)agg[6];
-    stats->worst_status = (int32_t)agg[7];
+    stats->n_steps = (int64_t)agg[1 * AS];
+    stats->n_reject = (int64_t)agg[2 * AS];
+    stats->n_sigma = (int64_t)agg[3 * AS];
+    stats->n_power_iter = (int64_t)agg[4 * AS];
+    stats->s_max_used = (int32_t)agg[5 * AS];
+    stats->n_failed = (int32_t)agg[6 * AS];
+    stats->worst_status = (int32_t)agg[7 * AS];
     stats->lanes_per_cell = li.G;
     stats->schedule = li.persistent ? RKC_SCHED_PERSISTENT : RKC_SCHED_PLAIN;
     stats->grid_blocks = li.blocks;
     stats->block_threads = li.threads;
     stats->lds_bytes = (int32_t)li.lds;
-    stats->n_rhs_slots = (int64_t)agg[8];
+    stats->n_rhs_slots = (int64_t)agg[8 * AS];
     stats->param_placement = li.RUC > 0 ? RKC_PARAMS_REGISTERS
                                         : (li.RUC == 0 ? RKC_PARAMS_LDS : RKC_PARAMS_GLOBAL);
 }
@@ -1589,7 +1590,7 @@ int rkc_integrate(const rkc_mech *mc, size_t n, double *T, const double *P, doub
         HIP_OK(hipStreamSynchronize(st));
     }
     if (stats) rkchost::fill_stats(agg, li, stats);
-    if (sync && agg[6] > 0) return RKC_ECELLS;
+    if (sync && agg[6 * rkcdev::AGG_STRIDE] > 0) return RKC_ECELLS;
     return RKC_OK;
 }
 

@@ -57,27 +57,46 @@ __device__ __forceinline__ int wmax_i(int x) {
     return x;
 }
 
-// `slots` is the number of source-term evaluations the wave issued (loop
-// iterations times groups per wave); with n_rhs it gives the fraction of
-// issued evaluations that advanced a cell.
-__device__ __forceinline__ void flush_agg(const Params &p, Agg a, bool leader,
-                                          unsigned long long slots) {
-    if (!leader) a = Agg{0, 0, 0, 0, 0, 0, 0, 0};
-    const unsigned long long r = wsum_u64(a.rhs), s = wsum_u64(a.steps), j = wsum_u64(a.rej),
-                             g = wsum_u64(a.sig), pi = wsum_u64(a.piter),
-                             f = wsum_u64((unsigned long long)a.failed);
-    const int sm = wmax_i(a.smax), w = wmax_i(a.worst);
-    if ((threadIdx.x & 63) == 0) {
-        atomicAdd(p.agg + 0, r);
-        atomicAdd(p.agg + 1, s);
-        atomicAdd(p.agg + 2, j);
-        atomicAdd(p.agg + 3, g);
-        atomicAdd(p.agg + 4, pi);
-        atomicMax(p.agg + 5, (unsigned long long)sm);
-        atomicAdd(p.agg + 6, f);
-        atomicMax(p.agg + 7, (unsigned long long)w);
-        atomicAdd(p.agg + 8, slots);
+// Totals of the workgroup's waves `v` (of lane 0) to the launch's counters, at the
+// kernel's end, through LDS that is no longer in use: one set of atomics per
+// workgroup.  One per wave, all on one line, held a launch of 3,072 waves up by
+// 315 us (13 species RKCK, 3,072 cells of 10 evaluations: 325 us).
+__device__ __forceinline__ void flush_block(const Params &p, const unsigned long long (&v)[AGG_USED],
+                                            unsigned char *lds, int wave) {
+    unsigned long long *w = reinterpret_cast<unsigned long long *>(lds);
+    const int lane = __lane_id();
+    __syncthreads();
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < AGG_USED; ++k) w[wave * AGG_USED + k] = v[k];
     }
+    __syncthreads();
+    const int waves = (blockDim.x + 63) / 64;
+    for (int k = wave * 64 + lane; k < AGG_USED; k += blockDim.x) {
+        const bool largest = k == 5 || k == 7;
+        unsigned long long t = 0;
+        for (int i = 0; i < waves; ++i) {
+            const unsigned long long x = w[i * AGG_USED + k];
+            t = largest ? max(t, x) : t + x;
+        }
+        if (t && largest) atomicMax(p.agg + k * AGG_STRIDE, t);
+        else if (t) atomicAdd(p.agg + k * AGG_STRIDE, t);
+    }
+}
+
+// Totals of the lanes that lead (in lane 0).  `slots` is the number of
+// source-term evaluations the wave issued (loop iterations times groups per
+// wave); with n_rhs it gives the fraction of issued evaluations that advanced a
+// cell.
+__device__ __forceinline__ void wave_totals(Agg a, bool leader, unsigned long long slots,
+                                            unsigned long long (&v)[AGG_USED]) {
+    if (!leader) a = Agg{0, 0, 0, 0, 0, 0, 0, 0};
+    v[0] = wsum_u64(a.rhs); v[1] = wsum_u64(a.steps); v[2] = wsum_u64(a.rej);
+    v[3] = wsum_u64(a.sig); v[4] = wsum_u64(a.piter);
+    v[5] = (unsigned long long)wmax_i(a.smax);
+    v[6] = wsum_u64((unsigned long long)a.failed);
+    v[7] = (unsigned long long)wmax_i(a.worst);
+    v[8] = slots;
 }
 
 // The kernel's parameter block (the only kernel argument, at the start of
@@ -265,6 +284,7 @@ constexpr double NORM2_ACCEPT = 0x1.0000000000001p0;
     const int groups = blockDim.x / G;                                                       \
     const int gib = threadIdx.x / G;                                                         \
     const int g = threadIdx.x % G;                                                           \
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64));                \
     const Shape sh = shape_of(p, G, RUC);                                                    \
     LdsPtrs lp = carve(lds_raw, sh, groups);                                                 \
     stage_tables(p, G, lp, RUC == 0 ? p.RU * G : 0, RUC >= 0);                               \
@@ -651,7 +671,9 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
             }
         }
     }
-    flush_agg(p, S.agg, g == 0, (unsigned long long)iters * (64 / G));
+    unsigned long long totals[AGG_USED];
+    wave_totals(S.agg, g == 0, (unsigned long long)iters * (64 / G), totals);
+    flush_block(p, totals, lds_raw, wave);
 }
 
 // ------------------------------------------------------------------ RKCK
@@ -869,7 +891,9 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
             }
         }
     }
-    flush_agg(p, S.agg, g == 0, (unsigned long long)iters * (64 / G));
+    unsigned long long totals[AGG_USED];
+    wave_totals(S.agg, g == 0, (unsigned long long)iters * (64 / G), totals);
+    flush_block(p, totals, lds_raw, wave);
 }
 
 }  // namespace rkcdev

@@ -45,9 +45,8 @@ struct WaveDesc {
 };
 const WaveDesc *wave_variants(int *n);
 
-// Aggregate counters per launch (n_rhs, n_steps, n_reject, n_sigma,
-// n_power_iter, s_max_used, n_failed, worst_status, issued slots; rest spare).
-constexpr int AGG_N = 16;
+// 8-byte words of a launch's aggregate counters.
+constexpr int AGG_N = rkcdev::AGG_USED * rkcdev::AGG_STRIDE;
 
 // What one integrator launch ran (for rkc_stats).
 struct LaunchInfo {
@@ -83,7 +82,7 @@ bool reserve_order(OrderScratch *s, size_t n, bool may_build);
 
 // Enqueue one integration of n cells whose arrays are device pointers on the
 // mechanism's device, with the launch's own scratch (aggregate counters
-// [16], work-queue head): launches that use distinct scratch may run
+// [AGG_N], work-queue head): launches that use distinct scratch may run
 // concurrently on different streams.  Not thread-safe for one mechanism
 // (its per-shape table cache is filled on first use).  With may_build false
 // nothing is allocated: RKC_ENOTSUP if the tables of the selected variant
@@ -102,7 +101,7 @@ int prepare(rkc_mech *m, const rkc_opts &o, size_t n_cells, OrderScratch *ord = 
 int mech_species(const rkc_mech *m);
 int mech_device(const rkc_mech *m);
 
-// Statistics of one launch from its aggregate counters ([16], see the kernels).
+// Statistics of one launch from its aggregate counters ([AGG_N], see the kernels).
 void fill_stats(const unsigned long long *agg, const LaunchInfo &li, rkc_stats *stats);
 
 }  // namespace rkchost

@@ -332,8 +332,15 @@ __device__ __forceinline__ void agg_lane(AggL &a, const Counts &c, int status) {
 }
 
 __device__ __forceinline__ void flush_lane(const Params &p, AggL &a, unsigned long long slots) {
-    flush_agg(p, Agg{a.rhs, a.steps, a.rej, a.sig, a.piter, a.smax, a.failed, a.worst}, true,
-              slots);
+    unsigned long long v[AGG_USED];
+    wave_totals(Agg{a.rhs, a.steps, a.rej, a.sig, a.piter, a.smax, a.failed, a.worst}, true, slots, v);
+    if (threadIdx.x % 64 == 0) {
+#pragma unroll
+        for (int k = 0; k < AGG_USED; ++k) {
+            if (k == 5 || k == 7) atomicMax(p.agg + k * AGG_STRIDE, v[k]);
+            else atomicAdd(p.agg + k * AGG_STRIDE, v[k]);
+        }
+    }
     a = AggL{0, 0, 0, 0, 0, a.smax, 0, a.worst};
 }
 

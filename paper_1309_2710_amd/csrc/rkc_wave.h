@@ -551,6 +551,7 @@ __device__ __forceinline__ double4 wave_recurrence(WaveState &S) {
 #define RKC_WAVE_PROLOGUE                                                                    \
     extern __shared__ __align__(16) unsigned char lds_raw[];                                 \
     constexpr int LANES = 64 * NW;                                                           \
+    const int wave = uni((int)(threadIdx.x / 64));                                           \
     /* TAIL: the cells that the lane groups handed over, instead of a queue */               \
     int n_tail = 0, at = (int)(threadIdx.x / LANES * gridDim.x + blockIdx.x);                \
     if constexpr (TAIL) {                                                                    \
@@ -601,18 +602,18 @@ __device__ __forceinline__ double4 wave_recurrence(WaveState &S) {
 
 #define RKC_WAVE_BOUNDS __launch_bounds__((NW > 1 ? 64 * NW : 256 * OCC), OCC)
 
-// Totals of a wave's cells; every evaluation it issued, all but `before` of
-// theirs, advanced one.
-__device__ __forceinline__ void flush_wave(const Params &p, const Agg &a, unsigned long long before) {
-    atomicAdd(p.agg + 0, a.rhs);
-    atomicAdd(p.agg + 1, a.steps);
-    atomicAdd(p.agg + 2, a.rej);
-    atomicAdd(p.agg + 3, a.sig);
-    atomicAdd(p.agg + 4, a.piter);
-    atomicMax(p.agg + 5, (unsigned long long)a.smax);
-    atomicAdd(p.agg + 6, (unsigned long long)a.failed);
-    atomicMax(p.agg + 7, (unsigned long long)a.worst);
-    atomicAdd(p.agg + 8, a.rhs - before);
+// Totals of the cells of the workgroup; every evaluation a wave issued, all but
+// `before` of theirs, advanced one.
+template <int NW>
+__device__ __forceinline__ void flush_wave(const Params &p, const Agg &a, unsigned long long before,
+                                           unsigned char *lds, int wave) {
+    unsigned long long v[AGG_USED] = {a.rhs, a.steps, a.rej, a.sig, a.piter,
+                                      (unsigned long long)a.smax, (unsigned long long)a.failed,
+                                      (unsigned long long)a.worst, a.rhs - before};
+    if (wave % NW != 0)   // the cell's first wave counts it
+#pragma unroll
+        for (int k = 0; k < AGG_USED; ++k) v[k] = 0;
+    flush_block(p, v, lds, wave);
 }
 
 RKC_WAVE_TEMPLATE
@@ -870,7 +871,7 @@ __global__ RKC_WAVE_BOUNDS void rkc_wave_kernel(Params p) {
         if (l < SG) store_state<SG, NSL>(p, cell, g, y);
         if (l == 0) { store_counts(p, cell, 0, c, fin); agg_cell(S.agg, c, fin); }
     }
-    if (l == 0) flush_wave(p, S.agg, done);
+    flush_wave<NW>(p, S.agg, done, lds_raw, wave);
 }
 
 RKC_WAVE_TEMPLATE
@@ -980,7 +981,7 @@ __global__ RKC_WAVE_BOUNDS void rkck_wave_kernel(Params p) {
         if (l < SG) store_state<SG, NSL>(p, cell, g, y);
         if (l == 0) { store_counts(p, cell, 0, c, fin); agg_cell(S.agg, c, fin); }
     }
-    if (l == 0) flush_wave(p, S.agg, done);
+    flush_wave<NW>(p, S.agg, done, lds_raw, wave);
 }
 
 }  // namespace rkcdev
