@@ -763,11 +763,14 @@ int plan_launch(const rkc_mech *m, const Choice &ch, const void *kernel, size_t 
 // unless the plain schedule or a grain is asked for, which only the lane-group
 // kernels have.  Where the line lies (MI355X, RKC, dt 1e-6, ms,
 // lane groups against waves):
-//   9 species, 16 lanes    1,024 cells 9.2 / 2.6    4,096 9.4 / 4.0   16,384 10.3 / 12.5
-//   13 species, 16 lanes   4,099 3.7 / 1.4         65,536 15.5 / 8.5  262,144 21.2 / 29.6
-//   53 species, 64 lanes   1,031 6.9 / 2.8         32,768 38.8 / 33.3 131,072 142 / 127
-//   53 species, falloff    1,031 13.7 / 6.1        16,411 29.6 / 34.3
-//   111 species            512 45 / 16              2,048 40 / 23     8,192 73.9 / 70
+//   9 species, 16 lanes    1,024 cells 9.2 / 2.3    9,000 7.6 / 6.3    24,000 11.2 / 14.5
+//   13 species, 16 lanes   4,099 3.7 / 1.2          9,000 2.5 / 1.7    24,000 5.4 / 4.8
+//   53 species, 64 lanes   1,031 6.9 / 2.5          32,768 38.8 / 29.9 131,072 142 / 117
+//   53 species, falloff    1,031 13.7 / 5.5         16,411 25.7 / 34.3
+//   111 species            512 45 / 16              2,048 40 / 23      8,192 73.9 / 65
+// RKCK cells of 16 lanes need less work between evaluations, and the line lies at
+// five times the count: 9 species 24,000 cells 3.6 / 2.7, 65,536 5.0 / 3.4, 262,144
+// 8.0 / 10.6; 13 species 24,000 0.30 / 0.16, 65,536 0.34 / 0.34, 131,072 0.46 / 0.61.
 const rkchost::WaveDesc *pick_wave(const rkc_mech *m, const Choice &ch, const NkTables *nk,
                                    size_t n, double atol, const rkc_opts &o, bool tail = false) {
     if (!nk || o.schedule == RKC_SCHED_PLAIN) return nullptr;
@@ -789,7 +792,8 @@ const rkchost::WaveDesc *pick_wave(const rkc_mech *m, const Choice &ch, const Nk
         if (rkcdev::wave_segments(nk->NSEG, d.SG, lanes) > d.MS || nk->SEGL > d.SL) continue;
         if (nk->L2P > d.LP || nk->L2N > d.LN) continue;
         const double resident = (double)(4 * d.occ / d.NW) * m->num_cus;
-        if (!tail && d.fill > 0.0 && (double)n > d.fill * resident) continue;
+        const double fill = o.method == RKC_METHOD_RKCK && d.SG == 16 ? 5.0 * d.fill : d.fill;
+        if (!tail && fill > 0.0 && (double)n > fill * resident) continue;
         if (tail && !d.k_rkc_tail) continue;
         return &d;
     }

@@ -34,9 +34,9 @@ namespace rkchost {
 // In order of preference: the first that fits the mechanism and the cell count
 // runs.  fill: the most cells per resident one (0: any number).
 static const WaveDesc kTable[] = {
-    RKC_WAVE_T(2.0, false, 16, 1, 1, rkcdev::UNITS_REG, 1, 1, 8, 4, 2),
-    RKC_WAVE_T(2.0, false, 16, 1, 1, rkcdev::UNITS_REG, 1, 1, 8, 4, 4),
-    RKC_WAVE_T(2.0, true, 16, 1, 1, rkcdev::UNITS_REG, 1, 1, 8, 4, 4),
+    RKC_WAVE_T(4.0, false, 16, 1, 1, rkcdev::UNITS_REG, 1, 1, 8, 4, 2),
+    RKC_WAVE_T(4.0, false, 16, 1, 1, rkcdev::UNITS_REG, 1, 1, 8, 4, 4),
+    RKC_WAVE_T(4.0, true, 16, 1, 1, rkcdev::UNITS_REG, 1, 1, 8, 4, 4),
     RKC_WAVE(1.125, 2, 64, 1, 3, rkcdev::UNITS_REG, 2, 2, 6, 8, 4),
     RKC_WAVE(0.0, 2, 64, 1, 5, rkcdev::UNITS_REG, 1, 4, 6, 8, 4),
     RKC_WAVE(0.0, 2, 64, 1, 5, rkcdev::UNITS_REG, 1, 3, 10, 8, 4),

@@ -90,9 +90,9 @@ def test_captured_call_and_graph_equal_eager(R, cfg, method):
 # was resident, when they queued, both methods, and steps whose stage counts or
 # error estimates take the rare branches
 @pytest.mark.parametrize("cfg,n,method,dt,kw", [
-    ("c1", 7000, 0, 3e-7, {}), ("c1", 20000, 1, 1e-8, {}), ("c2", 20001, 0, 1e-6, {}),
-    ("c2", 7001, 0, 1e-7, dict(stage_coefs=1)), ("c1", 7001, 0, 1e-6, dict(max_steps=40)),
-    ("c1", 7003, 0, 1e-6, dict(s_max=3)), ("c2", 7003, 0, 1e-6, dict(layout=1))])
+    ("c1", 13000, 0, 1e-7, {}), ("c1", 62001, 1, 1e-8, {}), ("c2", 20001, 0, 1e-6, {}),
+    ("c2", 13001, 0, 1e-7, dict(stage_coefs=1)), ("c1", 13001, 0, 1e-6, dict(max_steps=40)),
+    ("c1", 13003, 0, 3e-7, dict(s_max=3)), ("c2", 13003, 0, 1e-6, dict(layout=1))])
 def test_handed_over_cells_equal_plain(R, cfg, n, method, dt, kw):
     print("[case] hand-over", cfg, n, method, kw, flush=True)
     st = synth.config_states(cfg, n, seed=n)
