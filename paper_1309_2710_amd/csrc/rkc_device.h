@@ -146,7 +146,7 @@ constexpr int AGG_USED = 9, AGG_STRIDE = 16;
 // The work queue is dealt out in QUEUE_PARTS parts: claim i of part q is position
 // groups_total + i QUEUE_PARTS + q.  Claims on one address are served one by
 // one, 11.4 ns each from anywhere on the chip (a single head held 262,144 cells
-// of 10 evaluations to 1.75 ms, now 1.06); 16 heads on lines of their own take
+// of 10 evaluations to 1.75 ms, 16 to 1.06); 16 heads on lines of their own take
 // 0.7 ns, and 64 measured the same.
 constexpr int QUEUE_PARTS = 16, QUEUE_STRIDE = 32, QUEUE_INTS = QUEUE_PARTS * QUEUE_STRIDE;
 
@@ -156,7 +156,10 @@ constexpr int QUEUE_PARTS = 16, QUEUE_STRIDE = 32, QUEUE_INTS = QUEUE_PARTS * QU
 // groups that found it empty) a cell with more than TAIL_EVALS evaluations to go,
 // extrapolated over the rest of the interval, stops at its next step.  Its record:
 // the step control (16 words), then y, f(y) and the power method's vector.  The
-// waves look at the counts every TAIL_POLL evaluations.
+// waves look at the counts every TAIL_POLL evaluations.  Without / with it, ms: 9
+// species RKCK 262,144 cells 12.4 / 8.2; 13 species RKC 65,536 cells 11.1 / 7.3,
+// 262,144 21.2 / 18.7.  With 300 evaluations to go instead of 50: 13 species RKC
+// 9,000 cells 3.6 against 2.6.
 constexpr int QUEUE_IDLE = 1, QUEUE_TAIL = 2;   // ints of a part's line after its head
 constexpr int TAIL_DOUBLES = 64, TAIL_POLL = 64, TAIL_EVALS = 50;
 

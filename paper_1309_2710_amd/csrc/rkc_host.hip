@@ -982,7 +982,7 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
     // 9 species RKCK 262,144 cells 15.9 / 12.5; 13 species RKC 262,144 25.7 / 21.2;
     // 53 species falloff 16,411 29.5 / 25.7; 53 species 131,072 130.7 / 129.0;
     // 111 species 8,192 74.3 / 66.6; 13 species RKCK 262,144 (10 evaluations a
-    // cell) 1.06 / 1.10.  Not when every cell is resident: nothing queues.
+    // cell) 1.06 / 1.10, then without the totals' queue at the launch's end 0.7.  Not when every cell is resident: nothing queues.
     const bool ordered = ord && L.persistent && ch.v.G > 1 && n <= ORDER_MAX_CELLS &&
                          n > (size_t)L.blocks * (size_t)L.groups_per_block &&
                          reserve_order(ord, n, may_build);
