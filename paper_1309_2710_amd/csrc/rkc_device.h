@@ -39,6 +39,8 @@
 
 #include <type_traits>
 
+#include "rkc_queue.h"
+
 namespace rkcdev {
 
 constexpr double R_ERG = 8.31446261815324e7;   // erg/(mol K)
@@ -142,13 +144,6 @@ struct Params {
 // n_power_iter, s_max_used, n_failed, worst_status, issued slots), each on a line
 // of its own: atomics on one line are served one by one, 11.4 ns each.
 constexpr int AGG_USED = 9, AGG_STRIDE = 16;
-
-// The work queue is dealt out in QUEUE_PARTS parts: claim i of part q is position
-// groups_total + i QUEUE_PARTS + q.  Claims on one address are served one by
-// one, 11.4 ns each from anywhere on the chip (a single head held 262,144 cells
-// of 10 evaluations to 1.75 ms, 16 to 1.06); 16 heads on lines of their own take
-// 0.7 ns, and 64 measured the same.
-constexpr int QUEUE_PARTS = 16, QUEUE_STRIDE = 32, QUEUE_INTS = QUEUE_PARTS * QUEUE_STRIDE;
 
 // Hand-over of a lane-group launch's last cells to the one-cell-per-wave form,
 // which runs a cell 3 times faster but fills the chip with a fifth of the cells:

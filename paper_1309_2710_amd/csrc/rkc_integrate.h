@@ -112,43 +112,6 @@ __device__ __forceinline__ ParamsK *params_k() {
 // The same by reference, for functions that take the launch's arguments.
 __device__ __forceinline__ const Params &params_now() { return *(const Params *)params_k(); }
 
-// Claims on the work queue by groups of G lanes (64: one claim per wave; the
-// NW waves that share a cell claim together).  A group claims from its own part
-// until that is used up, then from the next; a part seen or claimed past its
-// end is never asked again.
-template <int G, int NW = 1>
-struct Claim {
-    int part, left;
-
-    __device__ __forceinline__ void init() {
-        // blocks and waves mixed: the first cells of waves with one number in
-        // their block are alike in an ordered queue
-        part = __builtin_amdgcn_readfirstlane(
-            (int)((blockIdx.x + threadIdx.x / (64 * NW)) % QUEUE_PARTS));
-        left = QUEUE_PARTS;
-    }
-    // unsigned: heads run past the end of the largest launches
-    __device__ __forceinline__ unsigned position(const Params &p, int i) const {
-        return (unsigned)(p.groups_total + part) + (unsigned)i * QUEUE_PARTS;
-    }
-    // the next position of the queue; n_cells once every part is used up
-    __device__ __forceinline__ int next(const Params &p, int g) {
-        while (left > 0) {
-            int i = 0;
-            if (g == 0) i = atomicAdd(p.queue + part * QUEUE_STRIDE, 1);
-            const unsigned pos = position(p, __shfl(i, 0, G));
-            if (pos < (unsigned)p.n_cells) return (int)pos;
-            do {
-                --left;
-                part = (part + 1) % QUEUE_PARTS;
-            } while (left > 0 &&
-                     position(p, __hip_atomic_load(p.queue + part * QUEUE_STRIDE, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT)) >= (unsigned)p.n_cells);
-        }
-        return p.n_cells;
-    }
-};
-
 // The cell at a queue position, -1 past the end.
 __device__ __forceinline__ int cell_at(const Params &p, int i) {
     if (i >= p.n_cells) return -1;
