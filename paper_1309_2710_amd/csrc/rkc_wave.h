@@ -37,6 +37,7 @@
 #pragma once
 
 #include "rkc_integrate.h"
+#include "rkc_wave_index.h"
 
 namespace rkcdev {
 
@@ -213,7 +214,8 @@ __device__ __forceinline__ void wave_setup(const Params &p, unsigned char *lds_r
     // every load is unconditional (clamped index), so that they are in flight together
 #pragma unroll
     for (int r = 0; r < RUC; ++r) {
-        // a lane past the last unit evaluates the empty record: 1 - 1 = 0, not gathered
+        // a lane past the last unit evaluates the empty record, without pressure
+        // dependence: 1 - 1 = 0, not gathered
         const int u = r * LANES + l;
         const bool used = u < p.nU;
         const double *rec = p.tab.units + (size_t)min(u, p.nU_pad - 1) * UNIT_DOUBLES;
@@ -295,7 +297,8 @@ template <int SG, int NSL, int RUC, int UL, int NW, int MS, int SL, int LP, int 
 __device__ __forceinline__ void rhs_wave(const double (&z)[NSL], double P10, double invP10,
                                          double (&fz)[NSL], const WaveLds &L,
                                          const WaveTab<NSL, RUC, UL, MS, SL, LP, LN> &w, const ExpK &K,
-                                         int g, int l, int N, int RUpw, int NMS, int pd0) {
+                                         int g, int l, int N, int RUpw, int NMS, int pd0,
+                                         int npd) {
     constexpr int NK = NSL * SG, LANES = 64 * NW;
     const double T = readlane_f64(z[0], 0);
 
@@ -403,10 +406,10 @@ __device__ __forceinline__ void rhs_wave(const double (&z)[NSL], double P10, dou
             kr = exp2_b31(arrhenius_arg(w.l2Ar[r], w.br[r], w.tr[r], l2T, invTa), K);
         }
         if constexpr (PD) {
-            const int u = r * LANES + l - pd0;   // place among the rounds with records
+            // the lanes past the last unit have no record
+            const int u = pdep_place(r * LANES + l, pd0, npd);
             if (r >= RUpw && u >= 0) {
-                const double2 *pd = reinterpret_cast<const double2 *>(L.pdep) +
-                                    (size_t)(6 * (u / SG)) * SG + u % SG;
+                const double2 *pd = reinterpret_cast<const double2 *>(L.pdep) + pdep_piece(u, 0, SG);
                 const double2 d0 = pd[0];
                 const uint64_t tag = __double_as_longlong(d0.x);
                 const int kind = (int)(tag & 0xffu);
@@ -576,6 +579,7 @@ __device__ __forceinline__ double4 wave_recurrence(WaveState &S) {
     WaveState &S = *L.state;                                                                 \
     const int l = threadIdx.x % LANES, g = threadIdx.x % SG;                                 \
     const int N = p.N, RUpw = p.n_plain / LANES, NMS = p.NMS, pd0 = p.RUp * SG;              \
+    const int npd = p.nU - pd0;   /* units with a record */                                 \
     const double u_round = 0x1p-53;                                                          \
     /* scalars that only the step control reads: in registers, or in LDS where the        */ \
     /* lane's share of a large mechanism needs the registers                              */ \
@@ -594,7 +598,7 @@ __device__ __forceinline__ double4 wave_recurrence(WaveState &S) {
     const ExpK K = exp_k_local();                                                            \
     auto rhs = [&](const double (&x)[NSL], double P10, double invP10, double (&f)[NSL]) {    \
         rhs_wave<SG, NSL, RUC, UL, NW, MS, SL, LP, LN, PD>(x, P10, invP10, f, L, w, K, g, l, N,  \
-                                                       RUpw, NMS, pd0);                      \
+                                                       RUpw, NMS, pd0, npd);                 \
     };
 
 #define RKC_WAVE_TEMPLATE                                                                    \
