@@ -861,6 +861,21 @@ int plan_rhs_launch(const rkc_mech *m, const Choice &ch, const NkTables *nk, con
 // percent of the launch.
 constexpr size_t ORDER_MAX_CELLS = (size_t)1 << 22;
 
+// The pass that classes cells by cost, for a launch L whose cells queue; *ordered is
+// false where none queue and where its counts find no room in LDS beside the tables
+// (the queue then runs in index order).
+int plan_order(const rkc_mech *m, const Choice &ch, const NkTables *nk, const Launch &L, size_t n,
+               bool *ordered, Launch *K) {
+    *ordered = false;
+    if (!L.persistent || ch.v.G == 1 || n > ORDER_MAX_CELLS ||
+        n <= (size_t)L.blocks * (size_t)L.groups_per_block)
+        return RKC_OK;
+    const int rc = plan_rhs_launch(m, ch, nk, m->n_pdep > 0 ? ch.v.k_rhs_pd : ch.v.k_rhs, n,
+                                   rkc_opts{}, 4 * rkcdev::ORDER_BINS, K);
+    *ordered = rc == RKC_OK;
+    return rc == RKC_ENOTSUP ? RKC_OK : rc;
+}
+
 void fill_params(const rkc_mech *m, const Choice &ch, const NkTables *nk, rkcdev::Params *p) {
     std::memset(p, 0, sizeof(*p));
     p->nS = m->nS;
@@ -983,9 +998,13 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
     // 53 species falloff 16,411 29.5 / 25.7; 53 species 131,072 130.7 / 129.0;
     // 111 species 8,192 74.3 / 66.6; 13 species RKCK 262,144 (10 evaluations a
     // cell) 1.06 / 1.10, then without the totals' queue at the launch's end 0.7.  Not when every cell is resident: nothing queues.
-    const bool ordered = ord && L.persistent && ch.v.G > 1 && n <= ORDER_MAX_CELLS &&
-                         n > (size_t)L.blocks * (size_t)L.groups_per_block &&
-                         reserve_order(ord, n, may_build);
+    bool ordered = false;
+    Launch K;
+    if (ord) {
+        rc = plan_order(m, ch, nk, L, n, &ordered, &K);
+        if (rc) return rc;
+        ordered = ordered && reserve_order(ord, n, may_build);
+    }
     {
         unsigned *hist = ordered ? ord->hist : nullptr;
         void *rargs[] = {&agg_d, &queue_d, &hist};
@@ -1032,9 +1051,6 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
     void *args[] = {&p};
     if (ordered) {
         const void *krhs = pd ? ch.v.k_rhs_pd : ch.v.k_rhs;
-        Launch K;
-        rc = plan_rhs_launch(m, ch, nk, krhs, n, rkc_opts{}, 4 * rkcdev::ORDER_BINS, &K);
-        if (rc) return rc;
         p.key = ord->key;
         p.hist = ord->hist;
         HIP_OK(hipLaunchKernel(krhs, dim3(K.blocks), dim3(K.threads), args, K.lds, st));
@@ -1131,10 +1147,11 @@ int prepare(rkc_mech *m, const rkc_opts &o, size_t n_cells, OrderScratch *ord) {
         }
     if (!ord) return RKC_OK;
     if (n_cells <= ORDER_MAX_CELLS) (void)reserve_order(ord, n_cells, true);
-    if (ch.v.G > 1)
+    if (ch.v.G > 1) {
         rc = plan_rhs_launch(m, ch, nk, pd ? ch.v.k_rhs_pd : ch.v.k_rhs, n_cells, rkc_opts{},
                              4 * rkcdev::ORDER_BINS, &L);
-    if (rc) return rc;
+        if (rc && rc != RKC_ENOTSUP) return rc;
+    }
     if (const rkchost::WaveDesc *td = pick_wave(m, ch, nk, n_cells, 1.0, o, true)) {
         (void)reserve_tail(ord, tail_cells(m, *td), true);
         for (const void *k : {td->k_rkc_tail, td->k_rkck_tail}) {
