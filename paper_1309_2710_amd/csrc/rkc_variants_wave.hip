@@ -4,29 +4,46 @@
 #include "rkc_internal.h"
 #include "rkc_wave.h"
 
+// A form's lanes per cell of the plan, once its LDS fits whatever the mechanism: all
+// its unit rounds pressure-dependent, with the most efficiency sets.  So no mechanism
+// that the host gives to a form is refused for LDS (the largest, 111 species with
+// falloff, takes 155,840 of 163,840 bytes).
+template <int SG, int NSL, int RUC, int UL, int NW, int MS, bool PD>
+constexpr int fits_lds() {
+    constexpr rkcdev::WaveShape sh{SG * NSL, 64 * NW, RUC, MS, PD ? RUC * 64 * NW / SG : 0,
+                                   PD ? rkcdev::MAX_EFFSETS : 0, SG, UL};
+    static_assert(rkcdev::wave_lds_bytes(sh, 1) <= 160 * 1024, "a form's workgroup exceeds LDS");
+    return SG;
+}
+
 #define RKC_WAVE_K(K_, ...)                                                                          \
     reinterpret_cast<const void *>(&rkcdev::K_##_wave_kernel<__VA_ARGS__>)
 
 #define RKC_WAVE(FILL_, OCC_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_)                         \
     rkchost::WaveDesc {                                                                              \
-        SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, OCC_, false, FILL_,                           \
+        fits_lds<SG_, NSL_, RUC_, UL_, NW_, MS_, false>(), NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, \
+            OCC_, false, FILL_,                                                                      \
             RKC_WAVE_K(rkc, OCC_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, false),             \
             RKC_WAVE_K(rkck, OCC_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, false),            \
             nullptr, nullptr                                                                         \
     }
 #define RKC_WAVE_PD(FILL_, OCC_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_)                      \
     rkchost::WaveDesc {                                                                              \
-        SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, OCC_, true, FILL_,                            \
+        fits_lds<SG_, NSL_, RUC_, UL_, NW_, MS_, true>(), NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_,  \
+            OCC_, true, FILL_,                                                                       \
             RKC_WAVE_K(rkc, OCC_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, true),              \
             RKC_WAVE_K(rkck, OCC_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, true),             \
             nullptr, nullptr                                                                         \
     }
 // also with the kernels that finish the cells handed over by 16-lane groups
-#define RKC_WAVE_T(FILL_, PD_, ...)                                                                  \
+#define RKC_WAVE_T(FILL_, PD_, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_)                        \
     rkchost::WaveDesc {                                                                              \
-        __VA_ARGS__, 3, PD_, FILL_, RKC_WAVE_K(rkc, 3, __VA_ARGS__, PD_),                            \
-            RKC_WAVE_K(rkck, 3, __VA_ARGS__, PD_), RKC_WAVE_K(rkc, 3, __VA_ARGS__, PD_, true),       \
-            RKC_WAVE_K(rkck, 3, __VA_ARGS__, PD_, true)                                              \
+        fits_lds<SG_, NSL_, RUC_, UL_, NW_, MS_, PD_>(), NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_,   \
+            3, PD_, FILL_,                                                                           \
+            RKC_WAVE_K(rkc, 3, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, PD_),                  \
+            RKC_WAVE_K(rkck, 3, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, PD_),                 \
+            RKC_WAVE_K(rkc, 3, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, PD_, true),            \
+            RKC_WAVE_K(rkck, 3, SG_, NSL_, RUC_, UL_, NW_, MS_, SL_, LP_, LN_, PD_, true)            \
     }
 
 namespace rkchost {

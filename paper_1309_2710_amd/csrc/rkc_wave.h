@@ -158,11 +158,11 @@ static_assert(sizeof(WaveState) <= 8 * WAVE_STATE, "wave state exceeds its LDS s
 __host__ __device__ inline int wave_segments(int NSEG, int SG, int lanes) {
     return (NSEG * SG + lanes - 1) / lanes;
 }
-__host__ __device__ inline size_t wave_cell_doubles(const WaveShape &s) {
+__host__ __device__ constexpr size_t wave_cell_doubles(const WaveShape &s) {
     return (size_t)s.NK + 2 + (size_t)s.RUC * s.lanes + 2 + (size_t)s.MS * s.lanes + 2 +
            (size_t)((s.NMS + 1) & ~1) + (size_t)WAVE_STATE * (s.lanes / 64);
 }
-__host__ __device__ inline size_t wave_lds_bytes(const WaveShape &s, int cells) {
+__host__ __device__ constexpr size_t wave_lds_bytes(const WaveShape &s, int cells) {
     return 8 * ((size_t)cells * wave_cell_doubles(s) + (size_t)NFIELD * s.NK + MUT_N +
                 (size_t)s.NPR * s.SG * PDEP_DOUBLES + (size_t)s.NMS * s.NK +
                 (s.UL == UNITS_LDS ? (size_t)6 * s.RUC * s.lanes : 0));
