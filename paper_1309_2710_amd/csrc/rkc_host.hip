@@ -967,30 +967,39 @@ int check_integrate_args(double dt, double rtol, double atol, const rkc_opts &o)
     return RKC_OK;
 }
 
-int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, double *Yd, double dt,
-                      double rtol, double atol, const rkc_opts &o, int32_t *sd, int32_t *cd,
-                      unsigned long long *agg_d, int *queue_d, hipStream_t st, LaunchInfo *li,
-                      bool may_build, OrderScratch *ord) {
+// The kernels of one integration, their launches, and the scratch they use.
+struct IntegratePlan {
     Choice ch;
-    NkTables *nk = nullptr;
-    int rc = select_variant(m, o, &ch, &nk, may_build);
-    if (rc) return rc;
-    const bool pd = m->n_pdep > 0;
-    const void *kernel = o.method == RKC_METHOD_RKC ? (pd ? ch.v.k_rkc_pd : ch.v.k_rkc)
-                                                    : (pd ? ch.v.k_rkck_pd : ch.v.k_rkck);
-    if (!kernel) return RKC_ENOTSUP;
+    NkTables *nk;
+    const void *kernel;
     Launch L;
-    const rkchost::WaveDesc *wd = pick_wave(m, ch, nk, n, atol, o);
-    if (wd) {
-        kernel = o.method == RKC_METHOD_RKC ? wd->k_rkc : wd->k_rkck;
-        rc = plan_wave_launch(m, *wd, nk, kernel, n, o, &L);
-    } else {
-        rc = plan_launch(m, ch, kernel, n, o, true, nk, &L);
-    }
+    const rkchost::WaveDesc *wave;   // the one-cell-per-wave form that runs, or null
+    bool ordered;                    // the queue, by the pass K
+    Launch K;
+    const void *tail_kernel;         // finishes handed-over cells in launch W, or null
+    Launch W;
+    size_t tail_cap;
+};
+
+// Plan an integration and reserve the scratch in `ord` of the passes that it has.
+static int plan_integrate(rkc_mech *m, size_t n, double atol, const rkc_opts &o, bool may_build,
+                          OrderScratch *ord, IntegratePlan *pl) {
+    int rc = select_variant(m, o, &pl->ch, &pl->nk, may_build);
     if (rc) return rc;
-    // launch errors are taken from the launch call itself: the thread's last
-    // error can hold an unrelated earlier status (e.g. a not-ready query made
-    // by other code in the process)
+    const bool pd = m->n_pdep > 0, rkc = o.method == RKC_METHOD_RKC;
+    const rkchost::VariantDesc &v = pl->ch.v;
+    pl->kernel = rkc ? (pd ? v.k_rkc_pd : v.k_rkc) : (pd ? v.k_rkck_pd : v.k_rkck);
+    if (!pl->kernel) return RKC_ENOTSUP;
+    pl->wave = pick_wave(m, pl->ch, pl->nk, n, atol, o);
+    if (pl->wave) {
+        pl->kernel = rkc ? pl->wave->k_rkc : pl->wave->k_rkck;
+        rc = plan_wave_launch(m, *pl->wave, pl->nk, pl->kernel, n, o, &pl->L);
+    } else {
+        rc = plan_launch(m, pl->ch, pl->kernel, n, o, true, pl->nk, &pl->L);
+    }
+    pl->ordered = false;
+    pl->tail_kernel = nullptr;
+    if (rc || !ord) return rc;
     // Cells that queue are taken in order of their expected cost: one evaluation
     // per cell and a sort (0.3 ms for 262,144 cells of 13 species) against a tail
     // of the longest cells, started last by chance.  In index order / ordered, ms:
@@ -998,21 +1007,43 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
     // 53 species falloff 16,411 29.5 / 25.7; 53 species 131,072 130.7 / 129.0;
     // 111 species 8,192 74.3 / 66.6; 13 species RKCK 262,144 (10 evaluations a
     // cell) 1.06 / 1.10, then without the totals' queue at the launch's end 0.7.  Not when every cell is resident: nothing queues.
-    bool ordered = false;
-    Launch K;
-    if (ord) {
-        rc = plan_order(m, ch, nk, L, n, &ordered, &K);
+    rc = plan_order(m, pl->ch, pl->nk, pl->L, n, &pl->ordered, &pl->K);
+    if (rc) return rc;
+    pl->ordered = pl->ordered && reserve_order(ord, n, may_build);
+    // The lane groups' last cells go to the wave form, all its resident waves
+    // having one.
+    const rkchost::WaveDesc *td =
+        pl->wave ? nullptr : pick_wave(m, pl->ch, pl->nk, n, atol, o, true);
+    if (td) {
+        const void *k = rkc ? td->k_rkc_tail : td->k_rkck_tail;
+        pl->tail_cap = tail_cells(m, *td);
+        rc = plan_wave_launch(m, *td, pl->nk, k, pl->tail_cap, rkc_opts{}, &pl->W);
         if (rc) return rc;
-        ordered = ordered && reserve_order(ord, n, may_build);
+        if (reserve_tail(ord, pl->tail_cap, may_build)) pl->tail_kernel = k;
     }
+    return RKC_OK;
+}
+
+int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, double *Yd, double dt,
+                      double rtol, double atol, const rkc_opts &o, int32_t *sd, int32_t *cd,
+                      unsigned long long *agg_d, int *queue_d, hipStream_t st, LaunchInfo *li,
+                      bool may_build, OrderScratch *ord) {
+    IntegratePlan pl;
+    const int rc = plan_integrate(m, n, atol, o, may_build, ord, &pl);
+    if (rc) return rc;
+    const Choice &ch = pl.ch;
+    const Launch &L = pl.L;
+    // launch errors are taken from the launch call itself: the thread's last
+    // error can hold an unrelated earlier status (e.g. a not-ready query made
+    // by other code in the process)
     {
-        unsigned *hist = ordered ? ord->hist : nullptr;
+        unsigned *hist = pl.ordered ? ord->hist : nullptr;
         void *rargs[] = {&agg_d, &queue_d, &hist};
         HIP_OK(hipLaunchKernel(reinterpret_cast<const void *>(&reset_scratch_kernel), dim3(1),
-                               dim3(ordered ? 1024 : 512), rargs, 0, st));
+                               dim3(pl.ordered ? 1024 : 512), rargs, 0, st));
     }
     rkcdev::Params p;
-    fill_params(m, ch, nk, &p);
+    fill_params(m, ch, pl.nk, &p);
     p.agg = agg_d;
     p.queue = queue_d;
     p.n_cells = (int)n;
@@ -1033,27 +1064,16 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
         p.ycs = 1;
         p.yss = (long long)n;
     }
-    // The lane groups' last cells go to the wave form, all its resident waves
-    // having one.
-    const rkchost::WaveDesc *td = wd || !ord ? nullptr : pick_wave(m, ch, nk, n, atol, o, true);
-    const void *tail_kernel = nullptr;
-    Launch W;
-    if (td) {
-        tail_kernel = o.method == RKC_METHOD_RKC ? td->k_rkc_tail : td->k_rkck_tail;
-        const size_t cap = tail_cells(m, *td);
-        rc = plan_wave_launch(m, *td, nk, tail_kernel, cap, rkc_opts{}, &W);
-        if (rc) return rc;
-        if (reserve_tail(ord, cap, may_build)) {
-            p.tail = ord->tail;
-            p.tail_cap = (int)cap;
-        }
+    if (pl.tail_kernel) {
+        p.tail = ord->tail;
+        p.tail_cap = (int)pl.tail_cap;
     }
     void *args[] = {&p};
-    if (ordered) {
-        const void *krhs = pd ? ch.v.k_rhs_pd : ch.v.k_rhs;
+    if (pl.ordered) {
+        const void *krhs = m->n_pdep > 0 ? ch.v.k_rhs_pd : ch.v.k_rhs;
         p.key = ord->key;
         p.hist = ord->hist;
-        HIP_OK(hipLaunchKernel(krhs, dim3(K.blocks), dim3(K.threads), args, K.lds, st));
+        HIP_OK(hipLaunchKernel(krhs, dim3(pl.K.blocks), dim3(pl.K.threads), args, pl.K.lds, st));
         int n_a = (int)n;
         void *oargs[] = {&ord->key, &ord->hist, &n_a, &ord->order};
         const int per = ORDER_THREADS * ORDER_PER_THREAD;
@@ -1063,12 +1083,14 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
         p.key = nullptr;
         p.order = ord->order;
     }
-    HIP_OK(hipLaunchKernel(kernel, dim3(L.blocks), dim3(L.threads), args, L.lds, st));
-    if (p.tail)
-        HIP_OK(hipLaunchKernel(tail_kernel, dim3(W.blocks), dim3(W.threads), args, W.lds, st));
+    HIP_OK(hipLaunchKernel(pl.kernel, dim3(L.blocks), dim3(L.threads), args, L.lds, st));
+    if (pl.tail_kernel)
+        HIP_OK(hipLaunchKernel(pl.tail_kernel, dim3(pl.W.blocks), dim3(pl.W.threads), args,
+                               pl.W.lds, st));
     li->G = ch.v.G;
-    li->RUC = !wd ? ch.v.RUC
-                  : wd->UL == rkcdev::UNITS_REG ? 1 : (wd->UL == rkcdev::UNITS_LDS ? 0 : -1);
+    li->RUC = !pl.wave ? ch.v.RUC
+                       : pl.wave->UL == rkcdev::UNITS_REG
+                             ? 1 : (pl.wave->UL == rkcdev::UNITS_LDS ? 0 : -1);
     li->persistent = L.persistent;
     li->blocks = L.blocks;
     li->threads = L.threads;
@@ -1127,39 +1149,11 @@ bool reserve_order(OrderScratch *s, size_t n, bool may_build) {
     return s->cap >= n;
 }
 
-int prepare(rkc_mech *m, const rkc_opts &o, size_t n_cells, OrderScratch *ord) {
-    Choice ch;
-    NkTables *nk = nullptr;
-    int rc = select_variant(m, o, &ch, &nk);
-    if (rc || n_cells == 0) return rc;
-    // sets the kernels' dynamic-LDS limit now rather than inside a capture
-    Launch L;
-    const bool pd = m->n_pdep > 0;
-    for (const void *k : {pd ? ch.v.k_rkc_pd : ch.v.k_rkc, pd ? ch.v.k_rkck_pd : ch.v.k_rkck}) {
-        if (!k) return RKC_ENOTSUP;
-        rc = plan_launch(m, ch, k, n_cells, o, true, nk, &L);
-        if (rc) return rc;
-    }
-    if (const rkchost::WaveDesc *wd = pick_wave(m, ch, nk, n_cells, 1.0, o))
-        for (const void *k : {wd->k_rkc, wd->k_rkck}) {
-            rc = plan_wave_launch(m, *wd, nk, k, n_cells, o, &L);
-            if (rc) return rc;
-        }
-    if (!ord) return RKC_OK;
-    if (n_cells <= ORDER_MAX_CELLS) (void)reserve_order(ord, n_cells, true);
-    if (ch.v.G > 1) {
-        rc = plan_rhs_launch(m, ch, nk, pd ? ch.v.k_rhs_pd : ch.v.k_rhs, n_cells, rkc_opts{},
-                             4 * rkcdev::ORDER_BINS, &L);
-        if (rc && rc != RKC_ENOTSUP) return rc;
-    }
-    if (const rkchost::WaveDesc *td = pick_wave(m, ch, nk, n_cells, 1.0, o, true)) {
-        (void)reserve_tail(ord, tail_cells(m, *td), true);
-        for (const void *k : {td->k_rkc_tail, td->k_rkck_tail}) {
-            rc = plan_wave_launch(m, *td, nk, k, tail_cells(m, *td), rkc_opts{}, &L);
-            if (rc) return rc;
-        }
-    }
-    return RKC_OK;
+int prepare(rkc_mech *m, const rkc_opts &o, size_t n_cells, double atol, OrderScratch *ord) {
+    // the plan also sets the kernels' dynamic-LDS limit, now rather than inside a capture
+    IntegratePlan pl;
+    if (n_cells > 0) return plan_integrate(m, n_cells, atol, o, true, ord, &pl);
+    return select_variant(m, o, &pl.ch, &pl.nk);
 }
 
 int mech_species(const rkc_mech *m) { return m->nS; }
@@ -1697,7 +1691,7 @@ int rkc_graph_create(const rkc_mech *mc, size_t n, double *T, const double *P, d
     if (hipMalloc(&g->agg_d, AGG_N * sizeof(unsigned long long)) != hipSuccess ||
         hipMalloc(&g->queue_d, rkcdev::QUEUE_INTS * sizeof(int)) != hipSuccess)
         rc = RKC_ENOMEM;
-    if (rc == RKC_OK) rc = rkchost::prepare(m, o, n, &g->order);
+    if (rc == RKC_OK) rc = rkchost::prepare(m, o, n, atol, &g->order);
     if (rc == RKC_OK &&
         hip_failed(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking), "hipStreamCreate",
                    __LINE__))

@@ -95,9 +95,10 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
 
 // Select the variant and build the device tables a later enqueue_integrate
 // with these options will use (so that concurrent launches only read them);
-// with n_cells > 0 also fix the kernels' launch attributes for that size and,
-// with `ord`, reserve the queue's scratch.
-int prepare(rkc_mech *m, const rkc_opts &o, size_t n_cells, OrderScratch *ord = nullptr);
+// with n_cells > 0 also fix the launch attributes of that launch's kernels and,
+// with `ord`, reserve the scratch it uses.
+int prepare(rkc_mech *m, const rkc_opts &o, size_t n_cells, double atol = 0.0,
+            OrderScratch *ord = nullptr);
 int mech_species(const rkc_mech *m);
 int mech_device(const rkc_mech *m);
 
