@@ -316,9 +316,12 @@ def _stream_handle(stream, tensors):
     if stream is not None:
         return ct.c_void_p(stream if isinstance(stream, int) else stream.cuda_stream)
     import torch
+    dev = tensors[0].get_device()
+    if dev < 0:
+        raise ValueError("expected a GPU tensor, got one on %s" % tensors[0].device)
     # the handle alone: building a Stream object around it costs 2 us, a fifth of
     # a small call
-    return ct.c_void_p(torch._C._cuda_getCurrentRawStream(tensors[0].get_device()))
+    return ct.c_void_p(torch._C._cuda_getCurrentRawStream(dev))
 
 
 def integrate(mech, T, P, Y, dt, rtol=1e-6, atol=1e-10, method=RKC, lanes_per_cell=0,
