@@ -320,8 +320,11 @@ def _stream_handle(stream, tensors):
     if dev < 0:
         raise ValueError("expected a GPU tensor, got one on %s" % tensors[0].device)
     # the handle alone: building a Stream object around it costs 2 us, a fifth of
-    # a small call
-    return ct.c_void_p(torch._C._cuda_getCurrentRawStream(dev))
+    # a small call; a private name, so not relied on
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return ct.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+    return ct.c_void_p(raw(dev))
 
 
 def integrate(mech, T, P, Y, dt, rtol=1e-6, atol=1e-10, method=RKC, lanes_per_cell=0,

@@ -21,3 +21,14 @@ def test_autotune_refuses_cpu_tensors(monkeypatch):
     with pytest.raises(ValueError):
         rkc.autotune(mech, T, P, Y, 1e-6)
     assert not calls
+
+
+def test_public_stream_where_the_raw_handle_is_missing(monkeypatch):
+    """The raw handle is a private name of torch: without it, the public call."""
+    t = types.SimpleNamespace(get_device=lambda: 3)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda d: 1000 + d)
+    assert rkc._stream_handle(None, [t]).value == 1003
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    monkeypatch.setattr(torch.cuda, "current_stream",
+                        lambda d: types.SimpleNamespace(cuda_stream=2000 + d))
+    assert rkc._stream_handle(None, [t]).value == 2003
