@@ -1015,7 +1015,31 @@ struct Occ {
     static constexpr int threads = waves * 256;
 };
 
-template <int G, int NSL, int RUC, bool PD>
+// The kernel's parameter block (the only kernel argument, at the start of
+// the kernarg segment) through a pointer the compiler cannot see through:
+// fields read through it are loaded with scalar loads where they are used,
+// instead of occupying scalar registers for the whole kernel.
+typedef const __attribute__((address_space(4))) Params ParamsK;
+__device__ __forceinline__ ParamsK *params_k() {
+    ParamsK *k = (ParamsK *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(k));
+    return k;
+}
+// The same by reference, for functions that take the launch's arguments.
+__device__ __forceinline__ const Params &params_now() { return *(const Params *)params_k(); }
+
+// Source term of a launch.  RHS_ONCE: one cell per group.  RHS_WALK: the grid covers
+// the chip once and walks over the cells, so the tables are staged once per resident
+// workgroup and not once per block of cells; the next cell's state loads while this
+// one is evaluated (species-major states come a cache line per species).  RHS_CLASS
+// walks and writes the cells' cost classes instead of F.  Bound by FP64 and LDS issue.
+// 13 species, 1,000,003 cells: 273 us with a block per 64 cells, 201 us walking; 53
+// species with falloff, 100,003 cells, species-major: 207 and 165 us.  A loop around
+// the evaluation holds its constants in scalar registers and spills 20 to 50 of them,
+// so launches that need no walk have a kernel without one: 9 species with falloff,
+// 12,289 cells 11.1 us, 12.4 in one turn of the loop.
+enum { RHS_ONCE = 0, RHS_WALK = 1, RHS_CLASS = 2 };
+template <int G, int NSL, int RUC, bool PD, int MODE>
 __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) void rhs_kernel(Params p) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int groups = blockDim.x / G;
@@ -1031,21 +1055,7 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
     UnitRegs<RUC> ur;
     load_unit_regs<RUC>(p, ur, g, G);
 
-    // The grid covers the chip once and walks over the cells, so the tables are
-    // staged once per resident workgroup and not once per block of cells; the
-    // next cell's state loads while this one is evaluated (species-major states
-    // come a cache line per species).  Bound by FP64 and LDS issue.  13 species,
-    // 1,000,003 cells: 273 us with a block per 64 cells, 201 us; 53 species with
-    // falloff, 100,003 cells, species-major: 207 and 165 us.
-    unsigned *hist = nullptr;
-    if (p.key) {
-        hist = reinterpret_cast<unsigned *>(lds_raw + lds_bytes(sh, groups));
-        for (int i = threadIdx.x; i < ORDER_BINS; i += blockDim.x) hist[i] = 0u;
-        __syncthreads();
-    }
-    const int stride = (int)gridDim.x * groups;
-    int cell = blockIdx.x * groups + gib;
-    double z[NSL], zn[NSL], fz[NSL], P = 1e5, Pn = 1e5;
+    double zn[NSL], fz[NSL], Pn = 1e5;   // the cell whose state loads
     auto load = [&](int c) {
 #pragma unroll
         for (int s = 0; s < NSL; ++s) {
@@ -1059,7 +1069,33 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
         }
         Pn = (c < p.n_cells) ? p.P[c] : 1e5;
     };
+    auto store = [&](int c) {
+        if (c < p.n_cells) {
+#pragma unroll
+            for (int s = 0; s < NSL; ++s) {
+                const int k = s * G + g;
+                if (k < p.N) p.F[(long long)c * p.fcs + (long long)k * p.fss] = fz[s];
+            }
+        }
+    };
+    int cell = blockIdx.x * groups + gib;
     load(cell);
+    if constexpr (MODE == RHS_ONCE) {
+        const double P10 = Pn * 10.0;
+        rhs_eval<G, NSL, RUC, PD>(zn, P10, 1.0 / P10, fz, L, ur, g, p.N, p.RU, p.NSEG, p.SEGL,
+                                  p.L2P, p.L2N, p.RUp, p.NMS, p.RU2, p.invTmax);
+        store(cell);
+        return;
+    }
+
+    double z[NSL], P;
+    unsigned *hist = nullptr;
+    if constexpr (MODE == RHS_CLASS) {
+        hist = reinterpret_cast<unsigned *>(lds_raw + lds_bytes(sh, groups));
+        for (int i = threadIdx.x; i < ORDER_BINS; i += blockDim.x) hist[i] = 0u;
+        __syncthreads();
+    }
+    const int stride = (int)gridDim.x * groups;
     while (__any(cell < p.n_cells)) {
 #pragma unroll
         for (int s = 0; s < NSL; ++s) z[s] = zn[s];
@@ -1067,9 +1103,18 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
         const int next = (cell < p.n_cells) ? cell + stride : cell;
         load(next);
         const double P10 = P * 10.0;
-        rhs_eval<G, NSL, RUC, PD>(z, P10, 1.0 / P10, fz, L, ur, g, p.N, p.RU, p.NSEG, p.SEGL,
-                                  p.L2P, p.L2N, p.RUp, p.NMS, p.RU2, p.invTmax);
-        if (p.key) {
+        // With falloff the arguments are read where they are used, which leaves one of
+        // 50 scalars spilled (53 species, 16,385 cells 34.7 us against 35.9); without, the
+        // reads cost more than the spills (13 species, 1,000,003 cells 211 us, 202)
+        if constexpr (PD) {
+            ParamsK &pr = *params_k();
+            rhs_eval<G, NSL, RUC, PD>(z, P10, 1.0 / P10, fz, L, ur, g, pr.N, pr.RU, pr.NSEG, pr.SEGL,
+                                      pr.L2P, pr.L2N, pr.RUp, pr.NMS, pr.RU2, pr.invTmax);
+        } else {
+            rhs_eval<G, NSL, RUC, PD>(z, P10, 1.0 / P10, fz, L, ur, g, p.N, p.RU, p.NSEG, p.SEGL,
+                                      p.L2P, p.L2N, p.RUp, p.NMS, p.RU2, p.invTmax);
+        }
+        if constexpr (MODE == RHS_CLASS) {
             // Cost class: the weighted square of the source term, which sets the
             // first step and ranks the cells' evaluation counts well enough that
             // starting with the largest brings the launch within 0 to 15 % of
@@ -1088,16 +1133,12 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
                 p.key[cell] = (uint16_t)b;
                 atomicAdd(&hist[b], 1u);
             }
-        } else if (cell < p.n_cells) {
-#pragma unroll
-            for (int s = 0; s < NSL; ++s) {
-                const int k = s * G + g;
-                if (k < p.N) p.F[(long long)cell * p.fcs + (long long)k * p.fss] = fz[s];
-            }
+        } else {
+            store(cell);
         }
         cell = next;
     }
-    if (p.key) {
+    if constexpr (MODE == RHS_CLASS) {
         __syncthreads();
         for (int i = threadIdx.x; i < ORDER_BINS; i += blockDim.x)
             if (hist[i]) atomicAdd(p.hist + i, hist[i]);

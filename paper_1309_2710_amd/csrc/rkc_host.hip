@@ -829,31 +829,44 @@ size_t tail_cells(const rkc_mech *m, const rkchost::WaveDesc &d) {
     return (size_t)(4 * d.occ) * (size_t)m->num_cus;
 }
 
-// Source-term launch of the lane-group variants: a grid that covers the chip
-// once (the kernel walks over the cells), in smaller workgroups while there are
-// too few cells to reach every compute unit, but with 512 lanes to stage the
-// tables; extra bytes of LDS follow the workgroup's own.
-int plan_rhs_launch(const rkc_mech *m, const Choice &ch, const NkTables *nk, const void *kernel,
-                    size_t n, const rkc_opts &o, size_t extra, Launch *L) {
+// Source-term launch of the lane-group variants: one cell per group while the chip
+// holds all of them at once, else a grid that covers it once and walks over the
+// cells (see rhs_kernel).  Workgroups of 512 lanes, which stage the tables, while
+// those reach every cell at once (512 lanes a compute unit), else the largest: 9
+// species, 7,000 cells 5.3 us against 6.3 in workgroups of 1,024 lanes; 53 species
+// with falloff, 4,097 cells 14.4 us in 768 lanes against 20.8 in 384.  `classes`: the
+// pass that classes cells by cost, with its counts behind the workgroup's LDS.
+int plan_rhs_launch(const rkc_mech *m, const Choice &ch, const NkTables *nk, size_t n,
+                    const rkc_opts &o, bool classes, const void **kernel, Launch *L) {
     const int G = ch.v.G;
+    const bool pd = m->n_pdep > 0;
+    const size_t cus = (size_t)m->num_cus, extra = classes ? 4 * rkcdev::ORDER_BINS : 0;
     const rkcdev::Shape sh = shape_for(ch, nk);
     int gpb = std::max(1, ch.v.max_threads / G);
-    if (o.block_groups > 0) {
-        gpb = std::min(gpb, o.block_groups);
-    } else {
-        while (gpb * G > 512 && (size_t)gpb * (size_t)m->num_cus > n) gpb = (gpb + 1) / 2;
-    }
+    if (o.block_groups > 0) gpb = std::min(gpb, o.block_groups);
+    else if ((size_t)(512 / G) * cus >= n) gpb = std::min(gpb, 512 / G);
     while (gpb > 1 && rkcdev::lds_bytes(sh, gpb) + extra > m->max_lds) --gpb;
     L->groups_per_block = gpb;
     L->threads = gpb * G;
     L->lds = rkcdev::lds_bytes(sh, gpb) + extra;
-    if (L->lds > m->max_lds) return RKC_ENOTSUP;
-    HIP_OK(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L->lds));
-    int per_cu = 0;
-    HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, L->threads, L->lds));
-    const size_t all = (n + gpb - 1) / gpb;
-    L->blocks = (int)std::min(all, (size_t)std::max(1, per_cu) * (size_t)m->num_cus);
     L->persistent = false;
+    if (L->lds > m->max_lds) return RKC_ENOTSUP;
+    const size_t all = (n + gpb - 1) / gpb;
+    const void *once = pd ? ch.v.k_rhs_pd : ch.v.k_rhs;
+    const void *walk = classes ? (pd ? ch.v.k_class_pd : ch.v.k_class)
+                               : (pd ? ch.v.k_walk_pd : ch.v.k_walk);
+    size_t resident = 0;
+    for (const void *k : {once, walk}) {
+        if (!k) return RKC_ENOTSUP;
+        if (k == once && classes) continue;
+        HIP_OK(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L->lds));
+        int per_cu = 0;
+        HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, L->threads, L->lds));
+        resident = (size_t)std::max(1, per_cu) * cus;
+        *kernel = k;
+        if (k == once && all <= resident) break;
+    }
+    L->blocks = (int)std::min(all, resident);
     return RKC_OK;
 }
 
@@ -865,13 +878,12 @@ constexpr size_t ORDER_MAX_CELLS = (size_t)1 << 22;
 // false where none queue and where its counts find no room in LDS beside the tables
 // (the queue then runs in index order).
 int plan_order(const rkc_mech *m, const Choice &ch, const NkTables *nk, const Launch &L, size_t n,
-               bool *ordered, Launch *K) {
+               bool *ordered, const void **kernel, Launch *K) {
     *ordered = false;
     if (!L.persistent || ch.v.G == 1 || n > ORDER_MAX_CELLS ||
         n <= (size_t)L.blocks * (size_t)L.groups_per_block)
         return RKC_OK;
-    const int rc = plan_rhs_launch(m, ch, nk, m->n_pdep > 0 ? ch.v.k_rhs_pd : ch.v.k_rhs, n,
-                                   rkc_opts{}, 4 * rkcdev::ORDER_BINS, K);
+    const int rc = plan_rhs_launch(m, ch, nk, n, rkc_opts{}, true, kernel, K);
     *ordered = rc == RKC_OK;
     return rc == RKC_ENOTSUP ? RKC_OK : rc;
 }
@@ -974,7 +986,8 @@ struct IntegratePlan {
     const void *kernel;
     Launch L;
     const rkchost::WaveDesc *wave;   // the one-cell-per-wave form that runs, or null
-    bool ordered;                    // the queue, by the pass K
+    bool ordered;                    // the queue, by class_kernel in launch K
+    const void *class_kernel;
     Launch K;
     const void *tail_kernel;         // finishes handed-over cells in launch W, or null
     Launch W;
@@ -1007,7 +1020,7 @@ static int plan_integrate(rkc_mech *m, size_t n, double atol, const rkc_opts &o,
     // 53 species falloff 16,411 29.5 / 25.7; 53 species 131,072 130.7 / 129.0;
     // 111 species 8,192 74.3 / 66.6; 13 species RKCK 262,144 (10 evaluations a
     // cell) 1.06 / 1.10, then without the totals' queue at the launch's end 0.7.  Not when every cell is resident: nothing queues.
-    rc = plan_order(m, pl->ch, pl->nk, pl->L, n, &pl->ordered, &pl->K);
+    rc = plan_order(m, pl->ch, pl->nk, pl->L, n, &pl->ordered, &pl->class_kernel, &pl->K);
     if (rc) return rc;
     pl->ordered = pl->ordered && reserve_order(ord, n, may_build);
     // The lane groups' last cells go to the wave form, all its resident waves
@@ -1070,10 +1083,10 @@ int enqueue_integrate(rkc_mech *m, size_t n, double *Td, const double *Pd, doubl
     }
     void *args[] = {&p};
     if (pl.ordered) {
-        const void *krhs = m->n_pdep > 0 ? ch.v.k_rhs_pd : ch.v.k_rhs;
         p.key = ord->key;
         p.hist = ord->hist;
-        HIP_OK(hipLaunchKernel(krhs, dim3(pl.K.blocks), dim3(pl.K.threads), args, pl.K.lds, st));
+        HIP_OK(hipLaunchKernel(pl.class_kernel, dim3(pl.K.blocks), dim3(pl.K.threads), args,
+                               pl.K.lds, st));
         int n_a = (int)n;
         void *oargs[] = {&ord->key, &ord->hist, &n_a, &ord->order};
         const int per = ORDER_THREADS * ORDER_PER_THREAD;
@@ -1519,7 +1532,7 @@ int rkc_rhs(const rkc_mech *mc, size_t n, const double *T, const double *P, cons
     const void *krhs = m->n_pdep > 0 ? ch.v.k_rhs_pd : ch.v.k_rhs;
     if (!krhs) return RKC_ENOTSUP;
     rc = ch.v.G == 1 ? plan_launch(m, ch, krhs, n, lo, false, nk, &L)
-                     : plan_rhs_launch(m, ch, nk, krhs, n, lo, 0, &L);
+                     : plan_rhs_launch(m, ch, nk, n, lo, false, &krhs, &L);
     if (rc) return rc;
     rkcdev::Params p;
     fill_params(m, ch, nk, &p);

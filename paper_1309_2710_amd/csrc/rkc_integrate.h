@@ -99,19 +99,6 @@ __device__ __forceinline__ void wave_totals(Agg a, bool leader, unsigned long lo
     v[8] = slots;
 }
 
-// The kernel's parameter block (the only kernel argument, at the start of
-// the kernarg segment) through a pointer the compiler cannot see through:
-// fields read through it are loaded with scalar loads where they are used,
-// instead of occupying scalar registers for the whole kernel.
-typedef const __attribute__((address_space(4))) Params ParamsK;
-__device__ __forceinline__ ParamsK *params_k() {
-    ParamsK *k = (ParamsK *)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(k));
-    return k;
-}
-// The same by reference, for functions that take the launch's arguments.
-__device__ __forceinline__ const Params &params_now() { return *(const Params *)params_k(); }
-
 // The cell at a queue position, -1 past the end.
 __device__ __forceinline__ int cell_at(const Params &p, int i) {
     if (i >= p.n_cells) return -1;

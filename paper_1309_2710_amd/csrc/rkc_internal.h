@@ -21,6 +21,10 @@ struct VariantDesc {
     const void *k_rkc_pd;
     const void *k_rkck_pd;
     const void *k_rhs_pd;
+    // the source term by a grid that walks over the cells, and the one that classes
+    // them by cost (null: one lane per cell)
+    const void *k_walk, *k_class;
+    const void *k_walk_pd, *k_class_pd;
 };
 
 const VariantDesc *variants_g64(int *n);
@@ -107,37 +111,36 @@ void fill_stats(const unsigned long long *agg, const LaunchInfo &li, rkc_stats *
 
 }  // namespace rkchost
 
+#define RKC_FN(...) reinterpret_cast<const void *>(&rkcdev::__VA_ARGS__)
+
 // A variant with plain-reaction kernels only (register-resident parameters).
 #define RKC_VARIANT(G_, NSL_, RUC_)                                                            \
     rkchost::VariantDesc {                                                                     \
         G_, NSL_, RUC_, (rkcdev::Occ<RUC_, NSL_>::threads),                                    \
-            reinterpret_cast<const void *>(&rkcdev::rkc_kernel<G_, NSL_, RUC_, false>),        \
-            reinterpret_cast<const void *>(&rkcdev::rkck_kernel<G_, NSL_, RUC_, false>),       \
-            reinterpret_cast<const void *>(&rkcdev::rhs_kernel<G_, NSL_, RUC_, false>),        \
-            nullptr, nullptr, nullptr                                                          \
+            RKC_FN(rkc_kernel<G_, NSL_, RUC_, false>),                                         \
+            RKC_FN(rkck_kernel<G_, NSL_, RUC_, false>),                                        \
+            RKC_FN(rhs_kernel<G_, NSL_, RUC_, false, rkcdev::RHS_ONCE>),                       \
+            nullptr, nullptr, nullptr,                                                         \
+            RKC_FN(rhs_kernel<G_, NSL_, RUC_, false, rkcdev::RHS_WALK>),                       \
+            RKC_FN(rhs_kernel<G_, NSL_, RUC_, false, rkcdev::RHS_CLASS>),                      \
+            nullptr, nullptr                                                                   \
     }
 
-// A variant with both kernel sets (parameters in LDS).
-// Plain and pressure-dependent kernels with the reaction parameters and the
-// species table in global memory (RUC = -1).
-#define RKC_VARIANT_PD_GLOBAL(G_, NSL_)                                                        \
+// Plain and pressure-dependent kernels.
+#define RKC_VARIANT_BOTH(G_, NSL_, RUC_)                                                       \
     rkchost::VariantDesc {                                                                     \
-        G_, NSL_, -1, (rkcdev::Occ<-1, NSL_>::threads),                                        \
-            reinterpret_cast<const void *>(&rkcdev::rkc_kernel<G_, NSL_, -1, false>),          \
-            reinterpret_cast<const void *>(&rkcdev::rkck_kernel<G_, NSL_, -1, false>),         \
-            reinterpret_cast<const void *>(&rkcdev::rhs_kernel<G_, NSL_, -1, false>),          \
-            reinterpret_cast<const void *>(&rkcdev::rkc_kernel<G_, NSL_, -1, true>),           \
-            reinterpret_cast<const void *>(&rkcdev::rkck_kernel<G_, NSL_, -1, true>),          \
-            reinterpret_cast<const void *>(&rkcdev::rhs_kernel<G_, NSL_, -1, true>)            \
+        G_, NSL_, RUC_, (rkcdev::Occ<RUC_, NSL_>::threads),                                    \
+            RKC_FN(rkc_kernel<G_, NSL_, RUC_, false>),                                         \
+            RKC_FN(rkck_kernel<G_, NSL_, RUC_, false>),                                        \
+            RKC_FN(rhs_kernel<G_, NSL_, RUC_, false, rkcdev::RHS_ONCE>),                       \
+            RKC_FN(rkc_kernel<G_, NSL_, RUC_, true>),                                          \
+            RKC_FN(rkck_kernel<G_, NSL_, RUC_, true>),                                         \
+            RKC_FN(rhs_kernel<G_, NSL_, RUC_, true, rkcdev::RHS_ONCE>),                        \
+            RKC_FN(rhs_kernel<G_, NSL_, RUC_, false, rkcdev::RHS_WALK>),                       \
+            RKC_FN(rhs_kernel<G_, NSL_, RUC_, false, rkcdev::RHS_CLASS>),                      \
+            RKC_FN(rhs_kernel<G_, NSL_, RUC_, true, rkcdev::RHS_WALK>),                        \
+            RKC_FN(rhs_kernel<G_, NSL_, RUC_, true, rkcdev::RHS_CLASS>)                        \
     }
-
-#define RKC_VARIANT_PD(G_, NSL_)                                                               \
-    rkchost::VariantDesc {                                                                     \
-        G_, NSL_, 0, (rkcdev::Occ<0, NSL_>::threads),                                          \
-            reinterpret_cast<const void *>(&rkcdev::rkc_kernel<G_, NSL_, 0, false>),           \
-            reinterpret_cast<const void *>(&rkcdev::rkck_kernel<G_, NSL_, 0, false>),          \
-            reinterpret_cast<const void *>(&rkcdev::rhs_kernel<G_, NSL_, 0, false>),           \
-            reinterpret_cast<const void *>(&rkcdev::rkc_kernel<G_, NSL_, 0, true>),            \
-            reinterpret_cast<const void *>(&rkcdev::rkck_kernel<G_, NSL_, 0, true>),           \
-            reinterpret_cast<const void *>(&rkcdev::rhs_kernel<G_, NSL_, 0, true>)             \
-    }
+// ... with the parameters in LDS, and with them and the species table in global memory.
+#define RKC_VARIANT_PD(G_, NSL_) RKC_VARIANT_BOTH(G_, NSL_, 0)
+#define RKC_VARIANT_PD_GLOBAL(G_, NSL_) RKC_VARIANT_BOTH(G_, NSL_, -1)

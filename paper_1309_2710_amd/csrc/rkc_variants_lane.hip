@@ -11,7 +11,8 @@
             reinterpret_cast<const void *>(&rkcdev::rhs_lane_kernel<NMAX_, false>),            \
             reinterpret_cast<const void *>(&rkcdev::rkc_lane_kernel<NMAX_, true>),             \
             reinterpret_cast<const void *>(&rkcdev::rkck_lane_kernel<NMAX_, true>),            \
-            reinterpret_cast<const void *>(&rkcdev::rhs_lane_kernel<NMAX_, true>)              \
+            reinterpret_cast<const void *>(&rkcdev::rhs_lane_kernel<NMAX_, true>),             \
+            nullptr, nullptr, nullptr, nullptr                                                 \
     }
 
 namespace rkchost {
