@@ -126,6 +126,7 @@ __device__ __forceinline__ void tail_idle(const Params &p, int g, int part) {
 // and then before: 4,096 waves reading the lines that the claims go to would hold
 // those up.
 __device__ __forceinline__ void tail_poll(const Params &p, unsigned iters, int cell, int &hands) {
+    if (!p.tail) return;
     if (p.persistent && !__any(cell < 0) && iters % 1024 != 0) return;
     int n = __hip_atomic_load(p.queue + (threadIdx.x % QUEUE_PARTS) * QUEUE_STRIDE + QUEUE_IDLE,
                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
