@@ -69,8 +69,11 @@ extern "C" {
 #define RKC_SCHED_PERSISTENT  2  /* resident grid; groups pull cells from a device queue,
                                     those of the largest expected cost first (in index
                                     order in served and no-allocation launches, in
-                                    launches that a caller captures, and past 2^22
-                                    cells) */
+                                    launches that a caller captures, past 2^22 cells
+                                    or 64 (RKCK 32) for each resident group, and where
+                                    the mechanism's tables leave less than 8 KB of LDS).
+                                    Without block_groups or grid_blocks a group may be
+                                    a whole wavefront or workgroup, as in _AUTO */
 
 /* ---- placement of reaction parameters (never changes results) --------- */
 #define RKC_PARAMS_AUTO       0  /* LDS (the measured faster placement), or global

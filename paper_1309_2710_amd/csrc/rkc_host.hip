@@ -761,13 +761,21 @@ int plan_launch(const rkc_mech *m, const Choice &ch, const void *kernel, size_t 
 // The one-cell-per-wave form for this call, or null for the lane-group kernels.
 // Both give the same bits, so the choice may depend on the cell count; it is made
 // unless the plain schedule or a grain is asked for, which only the lane-group
-// kernels have.  Where the line lies (MI355X, RKC, dt 1e-6, ms,
-// lane groups against waves):
-//   9 species, 16 lanes    1,024 cells 9.2 / 2.3    9,000 7.6 / 6.3    24,000 11.2 / 14.5
-//   13 species, 16 lanes   4,099 3.7 / 1.2          9,000 2.5 / 1.7    24,000 5.4 / 4.8
+// kernels have, and where a compiled form holds the mechanism: its units and the
+// segments, terms and pieces of its gather plan.  Where the line lies (MI355X, RKC,
+// dt 1e-6, ms, lane groups against waves):
+//   9 species, 16 lanes    1,024 cells 9.2 / 2.3    9,000 7.8 / 6.4    12,288 7.9 / 8.4
+//   13 species, 16 lanes   4,099 3.7 / 1.2          9,000 2.4 / 1.7    12,288 2.5 / 1.7
+//   with falloff  9 species 6,144 16.1 / 14.0       9,000 17.1 / 17.9  12,288 17.5 / 23.8
+//                 13 species                        9,000 2.6 / 1.8    12,288 2.6 / 2.0
 //   53 species, 64 lanes   1,031 6.9 / 2.5          32,768 38.8 / 29.9 131,072 142 / 117
-//   53 species, falloff    1,031 13.7 / 5.5         16,411 25.7 / 34.3
-//   111 species            512 45 / 16              2,048 40 / 23      8,192 73.9 / 65
+//   53 species, falloff    2,048 13.6 / 6.9         6,144 14.8 / 13.3  8,192 16.6 / 16.7
+//   111 species            512 45 / 16              6,145 97.8 / 52.7  8,192 64.0 / 64.4
+//   111 species, falloff   2,048 69.0 / 43.2        3,072 78.8 / 57.1  4,096 98.3 / 68.8
+// The lines suit launches that wait for their longest cells.  Cells of few, similar
+// counts favour the lane groups sooner (dt 1e-8: 111 species 8,192 cells 13.7 / 18.1,
+// with falloff 4,096 12.5 / 17.4; dt 1e-7: 9 species with falloff 12,288 14.3 / 15.0),
+// and long ones the waves later, and the counts are not known before the launch.
 // RKCK cells of 16 lanes need less work between evaluations, and the line lies at
 // five times the count: 9 species 24,000 cells 3.6 / 2.7, 65,536 5.0 / 3.4, 262,144
 // 8.0 / 10.6; 13 species 24,000 0.30 / 0.16, 65,536 0.34 / 0.34, 131,072 0.46 / 0.61.
@@ -870,18 +878,30 @@ int plan_rhs_launch(const rkc_mech *m, const Choice &ch, const NkTables *nk, siz
     return RKC_OK;
 }
 
-// Cells of a launch worth ordering: beyond this the queue's tail is under a
-// percent of the launch.
+// The most cells whose order is kept (25 MB).
 constexpr size_t ORDER_MAX_CELLS = (size_t)1 << 22;
 
+// Cells per resident group past which a queue is not ordered.  The pass and the sort
+// cost a little more than one evaluation per cell whatever the count; what they save
+// is at most the longest cell's time, a share of the launch that falls with the
+// rounds of cells.  Index order / ordered, RKC of 40 to 1,000 evaluations a cell: 4
+// rounds 1.02 to 1.95, 64 rounds 1.00 to 1.12.  RKCK: 6 or 7 evaluations a cell 16
+// rounds 0.80 to 1.01, 64 rounds 0.83 to 0.93; 130 and more (9 and 25 species, dt
+// 1e-8, rtol 1e-10) 18 to 36 rounds 1.23 to 1.41, 64 rounds 1.10 to 1.23.  Without the
+// line 53 species with falloff, RKCK, 1,048,576 cells took 12.9 ms, 11.6 before there
+// was an order and 11.4 now.
+constexpr size_t ORDER_ROUNDS_RKC = 64, ORDER_ROUNDS_RKCK = 32;
+
 // The pass that classes cells by cost, for a launch L whose cells queue; *ordered is
-// false where none queue and where its counts find no room in LDS beside the tables
-// (the queue then runs in index order).
+// false where none queue or too many, and where its counts find no room in LDS beside
+// the tables (the queue then runs in index order).
 int plan_order(const rkc_mech *m, const Choice &ch, const NkTables *nk, const Launch &L, size_t n,
-               bool *ordered, const void **kernel, Launch *K) {
+               int method, bool *ordered, const void **kernel, Launch *K) {
     *ordered = false;
-    if (!L.persistent || ch.v.G == 1 || n > ORDER_MAX_CELLS ||
-        n <= (size_t)L.blocks * (size_t)L.groups_per_block)
+    const size_t resident = (size_t)L.blocks * (size_t)L.groups_per_block;
+    const size_t rounds = method == RKC_METHOD_RKC ? ORDER_ROUNDS_RKC : ORDER_ROUNDS_RKCK;
+    if (!L.persistent || ch.v.G == 1 || n > ORDER_MAX_CELLS || n <= resident ||
+        n > rounds * resident)
         return RKC_OK;
     const int rc = plan_rhs_launch(m, ch, nk, n, rkc_opts{}, true, kernel, K);
     *ordered = rc == RKC_OK;
@@ -1018,9 +1038,8 @@ static int plan_integrate(rkc_mech *m, size_t n, double atol, const rkc_opts &o,
     // of the longest cells, started last by chance.  In index order / ordered, ms:
     // 9 species RKCK 262,144 cells 15.9 / 12.5; 13 species RKC 262,144 25.7 / 21.2;
     // 53 species falloff 16,411 29.5 / 25.7; 53 species 131,072 130.7 / 129.0;
-    // 111 species 8,192 74.3 / 66.6; 13 species RKCK 262,144 (10 evaluations a
-    // cell) 1.06 / 1.10, then without the totals' queue at the launch's end 0.7.  Not when every cell is resident: nothing queues.
-    rc = plan_order(m, pl->ch, pl->nk, pl->L, n, &pl->ordered, &pl->class_kernel, &pl->K);
+    // 111 species 8,192 74.3 / 66.6.
+    rc = plan_order(m, pl->ch, pl->nk, pl->L, n, o.method, &pl->ordered, &pl->class_kernel, &pl->K);
     if (rc) return rc;
     pl->ordered = pl->ordered && reserve_order(ord, n, may_build);
     // The lane groups' last cells go to the wave form, all its resident waves

@@ -16,9 +16,12 @@ def R():
 
 
 # all cells in the plain schedule (12.6 MB of scratch per step before), one lane per
-# cell, and few cells in the wave form (1.5 MB of records before)
-@pytest.mark.parametrize("n,kw", [(1 << 21, dict(schedule=1)), (1 << 21, dict(lanes_per_cell=1)),
-                                  (64, {})])
+# cell, few cells in the wave form (1.5 MB of records before), and queues of more
+# rounds of cells than are ordered (6.3 MB)
+@pytest.mark.parametrize("n,kw", [
+    (1 << 21, dict(schedule=1)), (1 << 21, dict(lanes_per_cell=1)), (64, {}),
+    (1 << 20, dict(lanes_per_cell=32, grid_blocks=1)),
+    (1 << 20, dict(lanes_per_cell=32, grid_blocks=1, method=1))])
 def test_scratch_only_where_used(R, n, kw):
     import torch
     print("[case] graph memory", n, kw, flush=True)
