@@ -154,9 +154,13 @@ constexpr int AGG_USED = 9, AGG_STRIDE = 16;
 // waves look at the counts every TAIL_POLL evaluations.  Without / with it, ms: 9
 // species RKCK 262,144 cells 12.4 / 8.2; 13 species RKC 65,536 cells 11.1 / 7.3,
 // 262,144 21.2 / 18.7.  With 300 evaluations to go instead of 50: 13 species RKC
-// 9,000 cells 3.6 against 2.6.
+// 9,000 cells 3.6 against 2.6.  With third-body and falloff reactions a wave hands
+// over after TAIL_AFTER_PD evaluations: launches that end soon after lose more to the
+// second kernel than its waves, which spill registers there, gain.  9 species, 12,289
+// cells, dt 1e-9: 0.73 without hand-over, 0.91 with it from the start, 0.70 after 128;
+// 13 species, 14,500 cells, dt 1e-6: 3.93 / 3.17 / 3.17, after 256 3.47.
 constexpr int QUEUE_IDLE = 1, QUEUE_TAIL = 2;   // ints of a part's line after its head
-constexpr int TAIL_DOUBLES = 64, TAIL_POLL = 64, TAIL_EVALS = 50;
+constexpr int TAIL_DOUBLES = 64, TAIL_POLL = 64, TAIL_EVALS = 50, TAIL_AFTER_PD = 128;
 
 // Cost classes of the ordered work queue: the top 11 bits of a positive float.
 constexpr int ORDER_BINS = 2048;

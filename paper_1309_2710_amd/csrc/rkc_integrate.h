@@ -125,8 +125,9 @@ __device__ __forceinline__ void tail_idle(const Params &p, int g, int part) {
 // Where cells queue, a wave looks once one of its own groups is idle, and now
 // and then before: 4,096 waves reading the lines that the claims go to would hold
 // those up.
+template <bool PD>
 __device__ __forceinline__ void tail_poll(const Params &p, unsigned iters, int cell, int &hands) {
-    if (!p.tail) return;
+    if (!p.tail || (PD && iters < TAIL_AFTER_PD)) return;
     if (p.persistent && !__any(cell < 0) && iters % 1024 != 0) return;
     int n = __hip_atomic_load(p.queue + (threadIdx.x % QUEUE_PARTS) * QUEUE_STRIDE + QUEUE_IDLE,
                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -320,7 +321,7 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
     for (;;) {
         if (!__any(S.cell >= 0)) break;   // a wave whose groups hold no cell issues nothing
         ++iters;
-        if (HANDS && iters % TAIL_POLL == 0) tail_poll(params_now(), iters, S.cell, S.hands);
+        if (HANDS && iters % TAIL_POLL == 0) tail_poll<PD>(params_now(), iters, S.cell, S.hands);
         {
             ParamsK &pr = *params_k();
             rhs_eval<G, NSL, RUC, PD>(z, S.P10, S.invP10, fz, L, ur, g, N, pr.RU, pr.NSEG, pr.SEGL,
@@ -715,7 +716,7 @@ __global__ __launch_bounds__((Occ<RUC, NSL>::threads), (Occ<RUC, NSL>::waves)) v
     for (;;) {
         if (!__any(S.cell >= 0)) break;   // a wave whose groups hold no cell issues nothing
         ++iters;
-        if (HANDS && iters % TAIL_POLL == 0) tail_poll(params_now(), iters, S.cell, S.hands);
+        if (HANDS && iters % TAIL_POLL == 0) tail_poll<PD>(params_now(), iters, S.cell, S.hands);
         {
             ParamsK &pr = *params_k();
             rhs_eval<G, NSL, RUC, PD>(z, S.P10, S.invP10, fz, L, ur, g, N, pr.RU, pr.NSEG, pr.SEGL,
