@@ -60,11 +60,13 @@ extern "C" {
 #define RKC_METHOD_RKCK  1      /* Sec. 2.3, Table 1 */
 
 /* ---- launch schedule (never changes results: see rkc_integrate) --------- */
-#define RKC_SCHED_AUTO        0  /* with few cells for the chip, one cell per wavefront (or
-                                    per workgroup, for large mechanisms), the lane groups'
-                                    arithmetic in the same order on more lanes; else as
-                                    RKC_SCHED_PERSISTENT, or _PLAIN when every cell is
-                                    resident */
+#define RKC_SCHED_AUTO        0  /* where a compiled form holds the mechanism and the cells
+                                    are few for the chip (39 to 63 species without
+                                    pressure-dependent reactions: any number), one cell
+                                    per wavefront or, for large mechanisms, per
+                                    workgroup: the lane groups' arithmetic in the same
+                                    order on more lanes; else as RKC_SCHED_PERSISTENT, or
+                                    _PLAIN when every cell is resident */
 #define RKC_SCHED_PLAIN       1  /* one lane group per cell, grid covers all cells */
 #define RKC_SCHED_PERSISTENT  2  /* resident grid; groups pull cells from a device queue,
                                     those of the largest expected cost first (in index
@@ -205,8 +207,13 @@ typedef struct {
     int32_t s_max_used;      /* largest RKC stage count any cell used */
     int32_t n_failed;        /* cells whose status is not RKC_CELL_OK */
     int32_t worst_status;    /* largest per-cell status code */
-    int32_t lanes_per_cell;  /* variant that ran */
+    int32_t lanes_per_cell;  /* variant that ran: the lane count whose order of sums the
+                                results have.  With one cell per wavefront or workgroup
+                                (see RKC_SCHED_AUTO) the cell's work is spread over 64 to
+                                512 lanes; the sums keep this order */
     int32_t schedule;        /* schedule that ran */
+    /* of the integrator's kernel, not of the passes before it (order) and after it (cells
+     * handed over to one wavefront each): */
     int32_t grid_blocks;     /* workgroups launched */
     int32_t block_threads;   /* threads per workgroup */
     int32_t lds_bytes;       /* dynamic LDS per workgroup */

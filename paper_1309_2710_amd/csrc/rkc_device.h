@@ -81,9 +81,10 @@ constexpr int MAX_EFFSETS = 16;
 
 struct Tables {
     const double *units;     // [RU * G][8]
-    const double *units_il;  // [RU + 1][4][G] double2: the same records lane-interleaved
-                             // as in LDS, one zero round after the last (read from
-                             // global memory by the RUC = -1 kernels)
+    const double *units_il;  // [RU and more][4][G] double2: the same records
+                             // lane-interleaved as in LDS, at least one zero round after
+                             // the last (read from global memory by the RUC = -1
+                             // kernels and the wave forms)
     const double *pdep;      // [NPR * G][12], interleaved by lane (rounds RUp..RU-1)
     const double *eff;       // [NMS][NK] third-body efficiencies by state index
     const double *spec;      // [NFIELD][NK]
