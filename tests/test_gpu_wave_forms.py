@@ -89,6 +89,32 @@ def test_forms_equal_lane_groups(R, name, n, method, layout):
     assert (a[2]["status"] == 0).all()
 
 
+# the options and counts whose comparison elsewhere holds on either kernel: they do run
+# the wave form (more cells than are resident, the recurrences of the coefficients, a
+# capped stage count, few steps), but with a zero tolerance
+@pytest.mark.parametrize("name,n,kw,wave", [
+    ("c1", 3079, {}, True), ("c2", 3077, {}, True), ("c3", 2051, dict(method=1), True),
+    ("c1", 33, dict(stage_coefs=1), True), ("c1", 33, dict(s_max=3), True),
+    ("c1", 33, dict(max_steps=7), True), ("c1", 33, dict(layout=1), True),
+    ("c1", 33, dict(lanes_per_cell=16), True), ("c1", 33, dict(lanes_per_cell=32), False),
+    ("c1", 33, dict(block_groups=4), False), ("c1", 33, dict(atol=0.0), False)])
+def test_which_calls_run_the_wave_form(R, name, n, kw, wave):
+    print("[case] form of", name, n, kw, flush=True)
+    m, cfg = _mech(name)
+    gm = R.Mechanism(m)
+    st = synth.config_states(cfg, n, seed=12)
+    kw = dict(kw)
+    atol, layout = kw.pop("atol", 1e-10), kw.get("layout", 0)
+    res = []
+    for more in ({}, dict(schedule=R.SCHED_PLAIN)):
+        T, Y = st["T"].copy(), np.array(st["Y"].T if layout else st["Y"], order="C")
+        out = R.integrate(gm, T, st["P"], Y, 1e-8, 1e-6, atol, counters=True, stats=True, **kw, **more)
+        res.append((T, Y, out))
+    a, b = res
+    assert (a[2]["stats"]["lds_bytes"] != b[2]["stats"]["lds_bytes"]) == wave
+    _same(a, b)
+
+
 def test_small_falloff_set_against_oracle(R):
     print("[case] 16-lane falloff against the oracle", flush=True)
     m, cfg = _mech("c2+pd")
